@@ -45,9 +45,7 @@ struct DevState {
 };
 
 // Search state of one RG step.  Candidate c of the current round has set-point
-// v[c]; tree nodes of a speculative bisection round keep their bracket in
-// a_lo/a_hi so that node kappa = (a_lo + a_hi) / 2 reproduces the arithmetic
-// of sequential bisection exactly.
+// v[c].
 struct DevSearch {
   // configuration
   int32_t mode, K, depth, M, refine, precision;
@@ -58,14 +56,13 @@ struct DevSearch {
   // per-step state
   double lo, hi;
   int32_t round, halvings, goal, done, found, status;
-  int32_t n_cand, probe, tree_base, tree_depth;
+  int32_t n_cand, probe;
   double kappa_res, v_res, worst_res;
   int32_t cand_total, rechecks_total, rounds_total, passes_alg1;
   // per candidate of the current round
   double kappa[kCMax];
   double v[kCMax];
   double mss[kCMax];
-  double a_lo[kCMax], a_hi[kCMax];
   unsigned long long key_all[kCMax];  // min over lanes of the FP32/FP64 rollout margin key
   unsigned long long key_far[kCMax];  // same, over lanes outside the recheck band
   unsigned long long key64[kCMax];    // min over FP64-rechecked lanes (ordered double)

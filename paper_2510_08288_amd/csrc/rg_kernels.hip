@@ -1677,49 +1677,45 @@ __device__ __forceinline__ double cand_worst(const DevSearch* S, int c) {
   return cand_worst_p(S, c, S->precision);
 }
 
-// Lay out a speculative bisection tree of `depth` levels over (lo, hi) at
-// candidates base.. (breadth-first; node q has children 2q+1 and 2q+2).
-__device__ void build_tree(DevSearch* S, int base, int depth, double lo, double hi) {
+// A speculative bisection tree of `depth` levels over (lo, hi) at candidates
+// base.. (breadth-first; node q has children 2q + 1 and 2q + 2), one thread per
+// node: each walks the levels above its own node, whose bracket it needs, in
+// registers.  Laid out by one thread, every node read its parent's bracket back
+// from device memory: about 0.7 us a node, 45 us for the 63 nodes of depth 6.
+__device__ __forceinline__ void build_tree(DevSearch* S, int base, int depth, double lo, double hi) {
   const int nn = (1 << depth) - 1;
-  S->a_lo[base] = lo;
-  S->a_hi[base] = hi;
-  S->kappa[base] = midpoint(lo, hi);
-  for (int q = 0; q < nn; ++q) {
-    const int c = base + q;
-    const double kq = S->kappa[c];
-    const int l = 2 * q + 1, r = 2 * q + 2;
-    if (l < nn) {
-      S->a_lo[base + l] = S->a_lo[c];
-      S->a_hi[base + l] = kq;
-      S->kappa[base + l] = midpoint(S->a_lo[c], kq);
+  for (int q = threadIdx.x; q < nn; q += blockDim.x) {
+    double a = lo, b = hi;
+    for (int level = 30 - __builtin_clz((unsigned)(q + 1)); level >= 0; --level) {
+      const double m = midpoint(a, b);
+      if (((q + 1) >> level) & 1) a = m;
+      else b = m;
     }
-    if (r < nn) {
-      S->a_lo[base + r] = kq;
-      S->a_hi[base + r] = S->a_hi[c];
-      S->kappa[base + r] = midpoint(kq, S->a_hi[c]);
-    }
+    S->kappa[base + q] = midpoint(a, b);
   }
-  S->tree_base = base;
-  S->tree_depth = depth;
 }
 
 // Thread-parallel per-candidate preparation: set-points, steady-state margins,
 // reduction accumulators.
 // Steady-state margins come from a small cache of recent set-points when
 // possible (the same v recurs from one RG step to the next while the governor
-// holds v or has reached r).
+// holds v or has reached r).  The cache takes this round's misses in candidate
+// order, the last kMssCache of them when there are more; the first wave ranks
+// them by ballots.  (One thread comparing every pair for duplicates through LDS
+// took 80 us at 63 candidates, most of the decision's launch.)
 template <int KIND>
 __device__ void prepare_candidates(const typename Plant<KIND, double>::Coef& pc, const DevState* st,
                                    DevSearch* S) {
   const double r = st->r, vp = st->v_prev;
-  __shared__ double s_cv[kMssCache], s_cm[kMssCache], s_v[kCMax];
+  __shared__ double s_cv[kMssCache], s_cm[kMssCache], s_v[kCMax], s_m[kCMax];
   __shared__ int s_miss[kCMax];
   for (int i = threadIdx.x; i < kMssCache; i += blockDim.x) {
     s_cv[i] = S->mss_v[i];
     s_cm[i] = S->mss_m[i];
   }
+  const int n = S->n_cand < kCMax ? S->n_cand : kCMax;
+  const int next = S->mss_next;
   __syncthreads();
-  const int n = S->n_cand;
   for (int c = threadIdx.x; c < n; c += blockDim.x) {
     if (S->mode != kNewton) S->full[c] = 0;
     // a speculative candidate of step t + j: that step's reference; its v_prev
@@ -1728,17 +1724,13 @@ __device__ void prepare_candidates(const typename Plant<KIND, double>::Coef& pc,
     const double v = cand_v(S->kappa[c], sj ? S->r_spec[sj - 1] : r, vp);
     S->v[c] = v;
     int hit = -1;
-    for (int i = 0; i < kMssCache; ++i) {
-      if (s_cv[i] == v) {
-        hit = i;
-        break;
-      }
-    }
-    S->mss[c] = hit >= 0 ? s_cm[hit] : steady_margin<KIND>(pc, S, v);
-    if (c < kCMax) {
-      s_miss[c] = hit < 0;
-      s_v[c] = v;
-    }
+#pragma unroll 8
+    for (int i = 0; i < kMssCache; ++i) hit = s_cv[i] == v ? i : hit;
+    const double m = hit >= 0 ? s_cm[hit] : steady_margin<KIND>(pc, S, v);
+    S->mss[c] = m;
+    s_miss[c] = hit < 0;
+    s_v[c] = v;
+    s_m[c] = m;
     S->key_all[c] = ~0ull;
     S->key_far[c] = ~0ull;
     S->key64[c] = ~0ull;
@@ -1749,20 +1741,36 @@ __device__ void prepare_candidates(const typename Plant<KIND, double>::Coef& pc,
     S->keyq[c] = ~0ull;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    S->n_recheck = 0;
-    int next = S->mss_next;
-    for (int c = 0; c < n && c < kCMax; ++c) {
-      if (!s_miss[c]) continue;
-      const double v = s_v[c];
-      bool dup = false;  // the same set-point twice in one round
-      for (int e = 0; e < c; ++e) dup = dup || (s_miss[e] && s_v[e] == v);
-      if (dup) continue;
-      S->mss_v[next] = v;
-      S->mss_m[next] = S->mss[c];
-      next = (next + 1) % kMssCache;
+  if (threadIdx.x < 64) {
+    static_assert(kCMax <= 128, "two candidates per lane of the first wave");
+    const int c0 = threadIdx.x, c1 = threadIdx.x + 64;
+    bool f0 = c0 < n && s_miss[c0], f1 = c1 < n && s_miss[c1];
+    const double v0 = c0 < n ? s_v[c0] : 0.0, v1 = c1 < n ? s_v[c1] : 0.0;
+#pragma unroll 4
+    for (int e = 0; e < n; ++e) {  // the same set-point twice in one round: its first only
+      const bool em = s_miss[e] != 0;
+      const double ev = s_v[e];
+      f0 = f0 && !(em && e < c0 && ev == v0);
+      f1 = f1 && !(em && e < c1 && ev == v1);
     }
-    S->mss_next = next;
+    const unsigned long long b0 = __builtin_amdgcn_ballot_w64(f0);
+    const unsigned long long b1 = __builtin_amdgcn_ballot_w64(f1);
+    const unsigned long long below = (1ull << threadIdx.x) - 1ull;
+    const int total = __builtin_popcountll(b0) + __builtin_popcountll(b1);
+    const int r0 = __builtin_popcountll(b0 & below);
+    const int r1 = __builtin_popcountll(b0) + __builtin_popcountll(b1 & below);
+    if (f0 && total - r0 <= kMssCache) {
+      S->mss_v[(next + r0) % kMssCache] = v0;
+      S->mss_m[(next + r0) % kMssCache] = s_m[c0];
+    }
+    if (f1 && total - r1 <= kMssCache) {
+      S->mss_v[(next + r1) % kMssCache] = v1;
+      S->mss_m[(next + r1) % kMssCache] = s_m[c1];
+    }
+    if (threadIdx.x == 0) {
+      S->n_recheck = 0;
+      S->mss_next = (next + total) % kMssCache;
+    }
   }
 }
 
@@ -1771,7 +1779,33 @@ template <int KIND>
 __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevState* st,
                            DevSearch* S, const double* r_seq, int closed_loop,
                            const RollArgs<KIND, double>* pa = nullptr) {
+  // Verdicts of the next speculated step's candidates, one lane each (at most
+  // 1 + K <= 41): bit l of s_adm / s_ref says candidate l of that step is
+  // certainly admitted / refused (below).  One thread reading them in turn, a
+  // device-memory round trip each, took 10 us at K = 12.
+  __shared__ unsigned long long s_adm, s_ref;
+  __shared__ int s_tree;  // levels of the tree that starts the step (0: none)
+  auto kall_of = [&](int c) {
+    return S->key_all[c] == ~0ull ? INFINITY : key_margin(S->key_all[c], S->precision);
+  };
+  if (threadIdx.x < 64 && closed_loop) {
+    int vd = -1;  // 1 admitted, 0 refused, -1 not certain
+    if (S->done && S->spec_used < S->spec_n && (int)threadIdx.x < S->spec_per) {
+      const int c = S->spec_base + S->spec_used * S->spec_per + threadIdx.x;
+      if (S->fail64[c]) vd = -1;
+      else if (S->dead[c] || S->mss[c] < 0.0) vd = 0;
+      else if (kall_of(c) >= S->band) vd = 1;
+    }
+    const unsigned long long adm = __builtin_amdgcn_ballot_w64(vd == 1);
+    const unsigned long long ref = __builtin_amdgcn_ballot_w64(vd == 0);
+    if (threadIdx.x == 0) {
+      s_adm = adm;
+      s_ref = ref;
+    }
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
+    s_tree = 0;
     if (closed_loop) st->r = r_seq[st->cl_index];
     // Was this step's first round already evaluated by an earlier round
     // (speculatively, from the state this step starts in if the steps before
@@ -1787,14 +1821,6 @@ __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevStat
     double spec_kappa = 0.0, spec_worst = -INFINITY;
     if (closed_loop && S->done && S->spec_used < S->spec_n) {
       const int base = S->spec_base + S->spec_used * S->spec_per;
-      auto kall_of = [&](int c) {
-        return S->key_all[c] == ~0ull ? INFINITY : key_margin(S->key_all[c], S->precision);
-      };
-      auto verdict = [&](int c) {  // 1 admitted, 0 refused, -1 not certain
-        if (S->fail64[c]) return -1;
-        if (S->dead[c] || S->mss[c] < 0.0) return 0;
-        return kall_of(c) >= S->band ? 1 : -1;
-      };
       // certain admission: every scenario's FP32 margin at least the band, so
       // no scenario violates (also under the chance-constrained verdict, whose
       // worst margin is the order statistic the round selected)
@@ -1807,21 +1833,17 @@ __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevStat
         spec_passes = passes;
       };
       if (S->spec_kind == 1) {
-        if (S->kappa_res == 1.0 && verdict(base) == 1) admit(base, 1);
+        if (S->kappa_res == 1.0 && (s_adm & 1ull)) admit(base, 1);
       } else if (S->kappa_res == 0.0) {  // the previous step held v
-        const int vb = verdict(base);
-        if (vb == 1) {
+        const int K = S->K;
+        const unsigned long long last = 1ull << K, all = (last << 1) - 1ull;
+        if (s_adm & 1ull) {
           admit(base, 1);
-        } else if (vb == 0) {
-          const int K = S->K;
-          int l = 1;
-          while (l <= K && verdict(base + l) == 0) ++l;
-          if (l > K) {
-            decided = true;
-            spec_passes = 1 + K;
-          } else if (l == K && verdict(base + K) == 1) {
-            admit(base + K, 1 + K);
-          }
+        } else if ((s_ref & all) == all) {
+          decided = true;
+          spec_passes = 1 + K;
+        } else if (K > 0 && (s_ref & all) == all - last && (s_adm & last)) {
+          admit(base + K, 1 + K);
         }
       }
       if (decided) S->spec_used += 1;
@@ -1886,14 +1908,12 @@ __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevStat
       S->n_cand = n;
       S->nk_idx = held ? -1 : 0;
       S->probe = 1;
-      S->tree_depth = 0;
       S->goal = S->K;
     } else if (S->mode == kGrid) {
       const int M = S->M;
       for (int i = 0; i < M; ++i) S->kappa[i] = (M > 1) ? (double)i / (double)(M - 1) : 1.0;
       S->n_cand = M;
       S->probe = 0;
-      S->tree_depth = 0;
       S->goal = S->refine;
     } else {
       S->kappa[0] = 1.0;
@@ -1905,7 +1925,6 @@ __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevStat
         // when it was 1, else every midpoint on the bisection path towards it.
         // The decision still takes each level's verdict from its own midpoint,
         // so the result is that of sequential bisection whatever the guess.
-        S->tree_depth = 0;
         if (pr >= 1.0) {
           S->n_cand = 1;
           // The probe alone fills few SIMDs: the round also runs the next
@@ -1969,8 +1988,7 @@ __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevStat
         }
       } else {
         const int d0 = S->K < S->depth ? S->K : S->depth;
-        if (d0 > 0) build_tree(S, 1, d0, 0.0, 1.0);
-        else S->tree_depth = 0;
+        s_tree = d0;
         S->n_cand = 1 + ((1 << d0) - 1);
       }
     }
@@ -1994,6 +2012,10 @@ __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevStat
     }
   }
   __syncthreads();
+  if (s_tree > 0) {  // uniform
+    build_tree(S, 1, s_tree, 0.0, 1.0);
+    __syncthreads();
+  }
   prepare_candidates<KIND>(pc, st, S);
 }
 
@@ -2106,128 +2128,164 @@ __device__ bool newton_decide(DevSearch* S, const DevGrad* G) {
 template <int KIND>
 __device__ void decide_body(const typename Plant<KIND, double>::Coef& pc, const DevState* st,
                             DevSearch* S, const DevGrad* grad) {
-  // Thread 0 may set S->done below: take the entry decision once, for the whole
-  // workgroup, so every wave reaches the same barriers.  The verdicts and worst
-  // margins of the round's candidates are staged in LDS by all threads first,
-  // so the sequential walk below reads no global memory in its loop.
-  __shared__ int s_done, s_n;
-  __shared__ double s_kappa[kCMax], s_worst[kCMax];
-  __shared__ unsigned char s_ok[kCMax], s_own[kCMax];
+  // Lane 0 may set S->done below: take the entry decision once, for the whole
+  // workgroup, so every wave reaches the same barriers.
+  __shared__ int s_done, s_more, s_depth;
+  __shared__ double s_lo, s_hi;
   if (threadIdx.x == 0) {
     s_done = S->done;
-    s_n = S->n_cand < kCMax ? S->n_cand : kCMax;
+    s_more = 0;
+    s_depth = 0;
   }
   __syncthreads();
   if (s_done) return;
-  if (S->mode != kNewton) {
-    for (int c = threadIdx.x; c < s_n; c += blockDim.x) {
-      s_kappa[c] = S->kappa[c];
-      s_ok[c] = cand_feasible(S, c) ? 1 : 0;
-      s_worst[c] = cand_worst(S, c);
-      s_own[c] = cand_step(S, c) == 0 ? 1 : 0;  // not a later step's speculative candidate
+  if (threadIdx.x < 64) {
+    // The first wave takes the decision: lane l holds candidates l and l + 64
+    // in registers, and each level of the walk finds its candidate by a ballot.
+    // (One thread searching the list in LDS at every level took 20 us at 63
+    // candidates.)
+    static_assert(kCMax <= 128, "two candidates per lane");
+    const int lane = threadIdx.x;
+    const int mode = S->mode, round = S->round, n_cand = S->n_cand;
+    const int n = n_cand < kCMax ? n_cand : kCMax;
+    double k0 = 0.0, k1 = 0.0, w0 = 0.0, w1 = 0.0;
+    bool ok0 = false, ok1 = false, own0 = false, own1 = false;
+    if (mode != kNewton) {
+      if (lane < n) {
+        k0 = S->kappa[lane];
+        ok0 = cand_feasible(S, lane);
+        w0 = cand_worst(S, lane);
+        own0 = cand_step(S, lane) == 0;  // not a later step's speculative candidate
+      }
+      if (lane + 64 < n) {
+        k1 = S->kappa[lane + 64];
+        ok1 = cand_feasible(S, lane + 64);
+        w1 = cand_worst(S, lane + 64);
+        own1 = cand_step(S, lane + 64) == 0;
+      }
     }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    S->rounds_total += 1;
-    S->cand_total += S->n_cand;
-    S->rechecks_total += S->n_recheck;
-    bool finished = false;
-    if (S->mode == kNewton) {
-      finished = newton_decide(S, grad);
-    } else if (S->mode == kGrid && S->round == 0) {
-      const int M = S->M;
-      int istar = -1;
-      for (int i = 0; i < M; ++i)
-        if (s_ok[i]) istar = i;
-      // Eq. (5) takes the largest all-admissible row even when a row below it
-      // was refused; say so in the step's diagnostics
-      for (int i = 0; i < istar; ++i)
-        if (!s_ok[i]) S->flags |= 1;
-      S->passes_alg1 += M;
-      if (istar < 0) {
-        finished = true;
-      } else {
-        S->found = 1;
-        S->worst_res = s_worst[istar];
-        S->lo = s_kappa[istar];
-        if (istar == M - 1) {
+    const unsigned long long m0 = __builtin_amdgcn_ballot_w64(ok0);
+    const unsigned long long m1 = __builtin_amdgcn_ballot_w64(ok1);
+    auto admitted = [&](int c) { return ((c < 64 ? m0 >> c : m1 >> (c - 64)) & 1ull) != 0; };
+    auto at = [&](double a0, double a1, int c) {  // lane c's value (c uniform)
+      return __shfl(c < 64 ? a0 : a1, c & 63);
+    };
+    bool finished = false, newton_more = false;
+    double lo = 0.0, hi = 0.0;
+    if (mode == kNewton) {
+      if (lane == 0) {
+        S->rounds_total += 1;
+        S->cand_total += n_cand;
+        S->rechecks_total += S->n_recheck;
+        finished = newton_decide(S, grad);
+        if (!finished) S->round = round + 1;
+        newton_more = !finished;
+      }
+    } else {
+      double worst = S->worst_res;
+      int halvings = S->halvings, passes = S->passes_alg1, found = S->found, flags = 0;
+      const int goal = S->goal;
+      lo = S->lo;
+      hi = S->hi;
+      if (mode == kGrid && round == 0) {
+        const int M = S->M;
+        const int istar = m1 ? 127 - __builtin_clzll(m1) : (m0 ? 63 - __builtin_clzll(m0) : -1);
+        passes += M;
+        if (istar < 0) {
           finished = true;
         } else {
-          S->hi = s_kappa[istar + 1];
-          if (S->goal <= 0) finished = true;
-        }
-      }
-    } else {
-      double lo = S->lo, hi = S->hi, worst = S->worst_res;
-      int halvings = S->halvings, passes = S->passes_alg1, found = S->found;
-      const int probe = S->probe, goal = S->goal, n = s_n;
-      if (probe) {
-        passes += 1;
-        if (s_ok[0]) {
+          // Eq. (5) takes the largest all-admissible row even when a row below
+          // it was refused; say so in the step's diagnostics
+          const int adm = __builtin_popcountll(m0) + __builtin_popcountll(m1);
+          if (adm != istar + 1) flags = 1;
           found = 1;
-          lo = 1.0;
-          worst = s_worst[0];
-          finished = true;
+          worst = at(w0, w1, istar);
+          lo = at(k0, k1, istar);
+          if (istar == M - 1) finished = true;
+          else hi = at(k0, k1, istar + 1);
+          if (goal <= 0) finished = true;
         }
-      }
-      if (!finished) {
-        // Sequential bisection over this round's candidates: each level takes
-        // the verdict of the candidate equal to the current midpoint (dyadic
-        // midpoints are exact, so equality identifies the node), until a
-        // midpoint was not evaluated this round.
-        while (halvings < goal) {
-          const double m = midpoint(lo, hi);
-          int c = -1;
-          for (int i = probe; i < n; ++i) {
-            if (s_kappa[i] == m && s_own[i]) {
-              c = i;
-              break;
-            }
-          }
-          if (c < 0) break;
+      } else {
+        const int probe = S->probe;
+        int cw = -1;  // the candidate whose worst margin stands
+        if (probe) {
           passes += 1;
-          if (s_ok[c]) {
-            lo = m;
+          if (admitted(0)) {
             found = 1;
-            worst = s_worst[c];
-          } else {
-            hi = m;
+            lo = 1.0;
+            cw = 0;
+            finished = true;
           }
-          halvings += 1;
         }
-        if (halvings >= goal) finished = true;
+        if (!finished) {
+          // Sequential bisection over this round's candidates: each level takes
+          // the verdict of the candidate equal to the current midpoint (dyadic
+          // midpoints are exact, so equality identifies the node), until a
+          // midpoint was not evaluated this round.
+          while (halvings < goal) {
+            const double m = midpoint(lo, hi);
+            const unsigned long long e0 =
+                __builtin_amdgcn_ballot_w64(own0 && lane >= probe && lane < n && k0 == m);
+            const unsigned long long e1 =
+                __builtin_amdgcn_ballot_w64(own1 && lane + 64 < n && k1 == m);
+            if (!(e0 | e1)) break;
+            const int c = e0 ? __builtin_ctzll(e0) : 64 + __builtin_ctzll(e1);
+            passes += 1;
+            if (admitted(c)) {
+              lo = m;
+              found = 1;
+              cw = c;
+            } else {
+              hi = m;
+            }
+            halvings += 1;
+          }
+          if (halvings >= goal) finished = true;
+        }
+        if (cw >= 0) worst = at(w0, w1, cw);
       }
-      S->lo = lo;
-      S->hi = hi;
-      S->worst_res = worst;
-      S->halvings = halvings;
-      S->passes_alg1 = passes;
-      S->found = found;
+      if (lane == 0) {
+        S->rounds_total += 1;
+        S->cand_total += n_cand;
+        S->rechecks_total += S->n_recheck;
+        if (flags) S->flags |= flags;
+        S->lo = lo;
+        S->hi = hi;
+        S->worst_res = worst;
+        S->halvings = halvings;
+        S->passes_alg1 = passes;
+        S->found = found;
+        if (!finished) {
+          const int rem = goal - halvings, depth = S->depth;
+          const int d = rem < depth ? rem : depth;
+          S->probe = 0;
+          S->spec_n = 0;  // the slots are reused; this step's kappa is below 1 anyway
+          S->spec_used = 0;
+          S->n_cand = (1 << d) - 1;
+          S->round = round + 1;
+          s_depth = d;
+          s_lo = lo;
+          s_hi = hi;
+        }
+      }
     }
-    if (finished) {
-      S->done = 1;
-      S->status = S->found ? (S->mode == kNewton && S->fallbacks > 0 ? 2 : 0) : 1;
-      S->kappa_res = S->found ? S->lo : 0.0;
-      S->pred = S->kappa_res;
-      S->v_res = S->found ? cand_v(S->kappa_res, st->r, st->v_prev) : st->v_prev;
-      if (!S->found) S->worst_res = -INFINITY;
-    } else if (S->mode != kNewton) {
-      const int rem = S->goal - S->halvings;
-      const int d = rem < S->depth ? rem : S->depth;
-      S->probe = 0;
-      S->spec_n = 0;  // the slots are reused; this step's kappa is below 1 anyway
-      S->spec_used = 0;
-      build_tree(S, 0, d, S->lo, S->hi);
-      S->n_cand = (1 << d) - 1;
-      S->round += 1;
-    } else {
-      S->round += 1;
+    if (lane == 0) {
+      if (finished) {
+        S->done = 1;
+        S->status = S->found ? (mode == kNewton && S->fallbacks > 0 ? 2 : 0) : 1;
+        S->kappa_res = S->found ? S->lo : 0.0;
+        S->pred = S->kappa_res;
+        S->v_res = S->found ? cand_v(S->kappa_res, st->r, st->v_prev) : st->v_prev;
+        if (!S->found) S->worst_res = -INFINITY;
+      }
+      s_more = newton_more || s_depth > 0;
     }
   }
-  __shared__ int s_more;
-  if (threadIdx.x == 0) s_more = !S->done;
   __syncthreads();
+  if (s_depth > 0) {  // uniform
+    build_tree(S, 0, s_depth, s_lo, s_hi);
+    __syncthreads();
+  }
   if (s_more) prepare_candidates<KIND>(pc, st, S);  // uniform: it has barriers
 }
 
