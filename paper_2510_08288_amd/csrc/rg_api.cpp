@@ -197,14 +197,22 @@ int lanes_for(const rg_handle* h) {
 
 int depth_for(const rg_handle* h, int lanes) {
   if (h->opt.depth > 0) return h->opt.depth;
-  // Enough candidates per round to give every SIMD of the chip up to four
-  // wavefronts (a round of few candidates is bound by one wave's latency, so
-  // more waves per SIMD come almost free), then the smallest depth that needs
-  // no more rounds.
+  // As many levels as keep a round's waves within the budget: up to it more
+  // candidates cost little (a round is bound by one wave's chain of steps),
+  // beyond it they cost their full time, while each level halves the bracket
+  // only once.  Then the smallest depth that needs no more rounds.
+  // 4-state plant: two waves per SIMD (4 lanes per scenario, FP32 quads and FP64
+  // matrix layout alike).  Per update, FP64: N = 1024 H = 1000 depth 3 / 4 / 5:
+  // 0.61 / 0.52 / 0.58 ms; N = 4096 H = 2000 depth 2 / 3 / 4: 1.57 / 1.48 /
+  // 1.65 ms.  Two levels at least: N = 16384 H = 1000 depth 1 / 2 / 3: 1.71 /
+  // 1.65 / 1.92 ms (half of the extra candidates die early).
+  // 9-state plant: four.
+  const bool lq4 = h->pr.p.kind == RG_PLANT_LQ4;
   const int goal = h->opt.search == RG_SEARCH_GRID ? h->opt.refine : h->opt.K;
-  const double lanes_budget = 4.0 * 256 * 4 * 64;
+  const double lanes_budget = (lq4 ? 2.0 : 4.0) * 256 * 4 * 64;
+  if (lq4 && h->opt.precision == RG_PREC_F64) lanes = 4;
   const double per_cand = (double)h->pr.s.N * lanes;
-  int dmax = 1;
+  int dmax = lq4 ? 2 : 1;
   while (dmax < 6 && ((1 << (dmax + 1)) - 1) * per_cand <= lanes_budget) ++dmax;
   if (goal <= 0) return 1;
   const int rounds = (goal + dmax - 1) / dmax;

@@ -16,174 +16,14 @@
 // No step reads back to the host.  All search state lives in DevSearch.
 #include <hip/hip_runtime.h>
 
-#include <cstring>
-#include <type_traits>
-
-#include "rg_device.hpp"
+#include "rg_lq4_mx.hpp"
 
 namespace rg {
-
-// ---------------------------------------------------------------------------
-// Argument blocks
-// ---------------------------------------------------------------------------
-template <int KIND, class T>
-struct RollArgs {
-  using P = Plant<KIND, T>;
-  typename P::Coef pc;
-  T F[kNC * P::ny];
-  T g[kNC];
-  T h, hh, h6;
-  T band;
-  int H, N;
-  int early, record, inject;
-  uint32_t seed, inst;
-  float wlo[P::nw], wspan[P::nw];
-  float thlo, thspan;
-  const float* wbuf;
-  const float* thbuf;
-  const DevState* st;
-  DevSearch* srch;
-  float* per_m;
-  int32_t* per_j;
-  unsigned long long* per_key;  // chance-constrained verdict: per-scenario margin keys
-  int2* rlist;
-  // checkpoints of one candidate's scenarios for the segment derivative:
-  // ckpt[(s * n + i) * N + k] = state component i of scenario k at step s * Kc
-  float* ckpt;
-  int Kc;
-  int ckpt_cand;  // that candidate (-1: the Newton iterate of the round)
-  // gen_row0 > 0: rows blockIdx.y >= gen_row0 of the launch generate the
-  // draws of step t + 1 into gen_w / gen_th instead of simulating
-  int gen_row0;
-  uint32_t gen_ofs;  // the draws generated are those of step t + gen_ofs
-  float* gen_w;
-  float* gen_th;
-  // forward tangent (CKPT = 2): per scenario of the tangent candidate, dm/dv
-  // (tan_dv[k]), the margin (per_m[k]) and its minimising step (per_j[k])
-  float* tan_dv;
-  // ring != 0 (closed loop): the draws of step s are in wring[s % kPairs],
-  // selected from the step counter on the device (wbuf, gen_w and gen_th are
-  // then unused; gen_w != nullptr only switches the draw workgroups on)
-  int ring;
-  float* wring[kPairs];
-  float* thring[kPairs];
-};
-
-// Draws of step t (streamed mode).
-template <class A>
-__device__ __forceinline__ const float* step_w(const A& a, uint32_t t) {
-  return a.ring ? a.wring[t % kPairs] : a.wbuf;
-}
-template <class A>
-__device__ __forceinline__ const float* step_th(const A& a, uint32_t t) {
-  return a.ring ? a.thring[t % kPairs] : a.thbuf;
-}
-
-template <int KIND>
-struct CtlArgs {
-  typename Plant<KIND, double>::Coef pc;
-  DevState* st;
-  DevSearch* srch;
-  const double* r_seq;
-  int closed_loop;
-  DevGrad* grad;
-};
-
-// ---------------------------------------------------------------------------
-// Draws
-// ---------------------------------------------------------------------------
-template <int NW>
-__device__ __forceinline__ void draw_w(uint32_t seed, uint32_t inst, uint32_t t, uint32_t tag,
-                                       uint32_t k, uint32_t j, const float* lo, const float* span,
-                                       float* w) {
-#pragma unroll
-  for (int blk = 0; blk < (NW + 3) / 4; ++blk) {
-    const Words r = philox10(k, j, t, (tag << 16) | (uint32_t)blk, seed, inst);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = 4 * blk + q;
-      if (c < NW) w[c] = box_draw(r.v[q], lo[c], span[c]);
-    }
-  }
-}
-
-template <int NTH>
-__device__ __forceinline__ void draw_theta_factor(uint32_t seed, uint32_t inst, uint32_t t,
-                                                  uint32_t k, float lo, float span, float* f) {
-#pragma unroll
-  for (int blk = 0; blk < (NTH + 3) / 4; ++blk) {
-    const Words r = philox10(k, 0u, t, (1u << 16) | (uint32_t)blk, seed, inst);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = 4 * blk + q;
-      if (c < NTH) f[c] = box_draw(r.v[q], lo, span);
-    }
-  }
-}
-
-// Streamed draws: w[(j * nw + c) * N + k] (consecutive scenarios contiguous, so
-// a wave's loads of one step coalesce), theta factors f[c * N + k].
-template <int KIND, class A>
-__device__ __forceinline__ void gen_body(const A& a, float* wbuf, float* thbuf, size_t gid,
-                                         uint32_t t, bool streaming = false) {
-  using P = Plant<KIND, float>;
-  const size_t nwork = (size_t)a.H * a.N;
-  if (gid < nwork) {
-    const int j = (int)(gid / a.N);
-    const int k = (int)(gid - (size_t)j * a.N);
-    float w[P::nw];
-    draw_w<P::nw>(a.seed, a.inst, t, 0u, (uint32_t)k, (uint32_t)j, a.wlo, a.wspan, w);
-#pragma unroll
-    for (int c = 0; c < P::nw; ++c) {
-      float* dst = &wbuf[((size_t)j * P::nw + c) * a.N + k];
-      if (streaming) __builtin_nontemporal_store(w[c], dst);
-      else *dst = w[c];
-    }
-  } else if (P::nth > 0 && gid < nwork + (size_t)a.N) {
-    const int k = (int)(gid - nwork);
-    float f[P::nth > 0 ? P::nth : 1];
-    draw_theta_factor<P::nth>(a.seed, a.inst, t, (uint32_t)k, a.thlo, a.thspan, f);
-#pragma unroll
-    for (int c = 0; c < P::nth; ++c) {
-      float* dst = &thbuf[(size_t)c * a.N + k];
-      if (streaming) __builtin_nontemporal_store(f[c], dst);
-      else *dst = f[c];
-    }
-  }
-}
 
 template <int KIND>
 __global__ void __launch_bounds__(256) k_gen(RollArgs<KIND, float> a, float* wbuf, float* thbuf,
                                              uint32_t t_ofs) {
   gen_body<KIND>(a, wbuf, thbuf, (size_t)blockIdx.x * blockDim.x + threadIdx.x, a.st->t + t_ofs);
-}
-
-// Draw rows of a rollout launch (grid-stride over the rows' threads): the
-// draws of step t + gen_ofs, or in the closed loop (ring) those of the steps
-// the step's setup chose (gen_lo .. gen_lo + gen_n - 1, in its first round
-// only).  Returns true in those rows.
-template <int KIND, class A>
-__device__ __forceinline__ bool gen_rows(const A& a) {
-  if (a.gen_row0 <= 0 || (int)blockIdx.y < a.gen_row0) return false;
-  uint32_t t1 = a.st->t + a.gen_ofs;
-  int nsteps = 1;
-  if (a.ring) {  // while the chunk has steps left
-    if (a.srch->round != 0 || a.st->cl_index >= a.st->cl_len) return true;
-    t1 = a.st->gen_lo;
-    nsteps = a.st->gen_n;
-  }
-  const size_t nth = (size_t)(gridDim.y - a.gen_row0) * gridDim.x * blockDim.x;
-  const size_t work = (size_t)a.H * a.N + (Plant<KIND, float>::nth > 0 ? (size_t)a.N : 0);
-  const size_t i0 =
-      ((size_t)(blockIdx.y - a.gen_row0) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-  for (int g = 0; g < nsteps; ++g, ++t1) {
-    float* gw = a.ring ? a.wring[t1 % kPairs] : a.gen_w;
-    float* gth = a.ring ? a.thring[t1 % kPairs] : a.gen_th;
-    // streaming stores: these draws are read steps later, and lines left dirty
-    // in L2 would have to be written back by the device-scope fences in between
-    for (size_t i = i0; i < work; i += nth) gen_body<KIND>(a, gw, gth, i, t1, true);
-  }
-  return true;
 }
 
 // A float or double moved between lanes by DPP (CTRL: quad permutations, row
@@ -710,45 +550,6 @@ __device__ __forceinline__ float rollout_lane_tan(const A& a, float v, int k, ui
   if (!finite) best = -INFINITY;
   dm = dbest;
   return best;
-}
-
-// Wave64 + workgroup minimum of a 64-bit key; returns the minimum in thread 0.
-__device__ __forceinline__ unsigned long long block_min_u64(unsigned long long v,
-                                                             unsigned long long* sh) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const uint32_t lo = __shfl_xor((uint32_t)v, off);
-    const uint32_t hi = __shfl_xor((uint32_t)(v >> 32), off);
-    const unsigned long long o = ((unsigned long long)hi << 32) | lo;
-    v = o < v ? o : v;
-  }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) sh[wave] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int nw = (blockDim.x + 63) >> 6;
-    for (int i = 1; i < nw; ++i) v = sh[i] < v ? sh[i] : v;
-  }
-  __syncthreads();
-  return v;
-}
-
-// Step offset of candidate c: 0 for the step's own candidates, j for a
-// speculative candidate of step t + j (closed loop, round 0).
-__device__ __forceinline__ int cand_step(const DevSearch* S, int c) {
-  const int r = c - S->spec_base;
-  return (S->spec_n > 0 && r >= 0 && r < S->spec_n * S->spec_per) ? 1 + r / S->spec_per : 0;
-}
-
-// In decision mode a candidate whose FP64 steady-state test already fails is
-// refused without simulating it (the verdict of Alg. 1 needs both tests).
-// bx: the workgroup's scenario tile (tile 0 raises the flag).
-__device__ __forceinline__ bool refused_by_steady_state(int early, DevSearch* S, int c,
-                                                        int bx = -1) {
-  if (!early || !(S->mss[c] < 0.0)) return false;
-  if ((bx < 0 ? (int)blockIdx.x : bx) == 0 && threadIdx.x == 0)
-    __hip_atomic_store(&S->dead[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return true;
 }
 
 // Main rollout kernel: blockIdx.y = candidate of the round, blockIdx.x * block
@@ -1278,138 +1079,59 @@ __global__ void __launch_bounds__(256) k_rollout_lq4_quad(const RollArgs<1, floa
   }
 }
 
-// FP64 re-simulation of the near-band list, LQ4 with one entry per quad of
-// lanes (the layout of the FP32 quad rollout, in double precision: a 64-bit
-// DPP exchange is two 32-bit ones).  Same verdict as the one-lane recheck.
-struct QuadCoef64 {
-  double a[4][4], g[4][4], d[4][4];
-  double b[4];
-  double e[4][2];
-  double grow[4];
-};
-
-__device__ __forceinline__ double min2d(double a, double b) { return b < a ? b : a; }
-
-__device__ __forceinline__ double quad_min64(double m) {
-  m = min2d(m, dpp64<kSwap1>(m));
-  return min2d(m, dpp64<kSwap2>(m));
-}
-
+// FP64 re-simulation of the near-band list, 4-state plant on the matrix cores:
+// a wave takes 16 entries (lanes past the list repeat its last one and drop the
+// result).  An entry is settled once it violates or its candidate has been
+// refused; the wave ends when all of its entries are.
 template <int RNG, int INJ>
-__global__ void __launch_bounds__(256) k_recheck_lq4_quad(const RollArgs<1, double> a,
-                                                         const QuadCoef64 qc,
-                                                         const CtlArgs<1> ctl, int decide) {
-  constexpr int U = kQuadGroup;
+__global__ void __launch_bounds__(256, 2) k_recheck_lq4_mx(const RollArgs<1, double> a,
+                                                           const MxCoef mc,
+                                                           const CtlArgs<1> ctl, int decide) {
   DevSearch* S = a.srch;
   if (S->done) return;
   const int n = S->n_recheck;
   const uint32_t t = a.st->t;
-  const int q = threadIdx.x & 3;
-  const double A0 = qc.a[q][0], A1 = qc.a[q][1], A2 = qc.a[q][2], A3 = qc.a[q][3];
-  const double G0 = qc.g[q][0], G1 = qc.g[q][1], G2 = qc.g[q][2], G3 = qc.g[q][3];
-  const double d0 = qc.d[q][0], d1 = qc.d[q][1], d2 = qc.d[q][2], d3 = qc.d[q][3];
-  const double e0 = qc.e[q][0], e1 = qc.e[q][1], grow = qc.grow[q], bq = qc.b[q];
-  const double h = a.h, hh = a.hh, h6 = a.h6;
-  const int H = a.H;
-  const uint32_t row_bytes = 8u * (uint32_t)a.N;
-  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)step_w(a, t), (short)0, (int)(row_bytes * (uint32_t)(H + U)), 0x00020000);
-  const int stride = (int)((gridDim.x * blockDim.x) >> 2);
+  const int lane = threadIdx.x & 63, q = lane >> 4;
+  const int waves = (int)((gridDim.x * blockDim.x) >> 6);
   // chance-constrained verdict (qv > 0): one FP64 violation refuses the
   // candidate only once more than qv scenarios violate, so an entry does not
   // stop on another's, and every entry keeps its margin key
   const int qv = S->q;
-  // every lane of a quad holds the same entry, so all exits are quad-uniform
-  for (int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 2); i < n; i += stride) {
-    const int2 en = a.rlist[i];
+  for (int w = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6); 16 * w < n; w += waves) {
+    const int i = 16 * w + (lane & 15);
+    const bool live = i < n;
+    const int2 en = a.rlist[live ? i : n - 1];
     const int c = en.x, k = en.y;
-    if (a.early &&
-        (__hip_atomic_load(&S->dead[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-         __hip_atomic_load(&S->fail64[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-      continue;
-    const double bv = bq * S->v[c];
-    double x = a.st->x[q];
-    auto deriv = [&](double s, double xv) {
-      const double c2 = __builtin_fma(G2, xv, A2) * xv;
-      const double c3 = __builtin_fma(G3, xv, A3) * xv;
-      double c0 = __builtin_fma(__builtin_fma(G0, xv, A0), xv, s);
-      double c1 = __builtin_fma(G1, xv, A1) * xv;
-      c1 = c1 + dpp64<kSwap2>(c3);
-      c0 = c0 + dpp64<kSwap2>(c2);
-      return c0 + dpp64<kSwap1>(c1);
+    auto refused = [&]() {
+      return __hip_atomic_load(&S->fail64[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     };
-    auto row_margin = [&](double xv) {
-      const double c2 = d2 * xv, c3 = d3 * xv;
-      double c0 = __builtin_fma(d0, xv, grow);
-      double c1 = d1 * xv;
-      c1 = c1 + dpp64<kSwap2>(c3);
-      c0 = c0 + dpp64<kSwap2>(c2);
-      return c0 + dpp64<kSwap1>(c1);
-    };
-    double bm = row_margin(x);  // lane q: running minimum of row q
-    const uint32_t vo0 = 4u * (uint32_t)k, vo1 = vo0 + 4u * (uint32_t)a.N;
-    uint32_t so = 0;
-    auto load_group = [&](int j, float* w) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (RNG == 0) {
-          const uint32_t sr = so + (uint32_t)u * row_bytes;
-          w[2 * u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, vo0, sr, 0));
-          w[2 * u + 1] =
-              __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, vo1, sr, 0));
-        } else {
-          const Words r = philox10((uint32_t)k, (uint32_t)(j + u), t, 0u, a.seed, a.inst);
-          w[2 * u] = box_draw(r.v[0], a.wlo[0], a.wspan[0]);
-          w[2 * u + 1] = box_draw(r.v[1], a.wlo[1], a.wspan[1]);
-        }
+    const bool skip =
+        a.early &&
+        (__hip_atomic_load(&S->dead[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || refused());
+    if (__builtin_amdgcn_ballot_w64(!skip) == 0) continue;
+    struct Stop {
+      const decltype(refused)& ref;
+      int early, qv, g;
+      bool skip;
+      __device__ __forceinline__ void begin() {}
+      __device__ __forceinline__ bool end(double bm) {
+        if (!early) return false;
+        ++g;
+        const bool poll = (g & 7) == 0 && qv == 0;
+        const bool settled = skip || bm < 0.0 || (poll && ref());
+        const uint32_t open = 0xffffu & ~mx_scenarios(settled);
+        return open == 0;
       }
-      if (RNG == 0) so += (uint32_t)U * row_bytes;
-    };
-    auto step = [&](float w0f, float w1f) {
-      const double w0 = (double)w0f, w1 = (double)w1f;
-      const double s = INJ == 0 ? __builtin_fma(e1, w1, __builtin_fma(e0, w0, bv)) : bv;
-      const double k1 = deriv(s, x);
-      double acc = k1;
-      double xs = __builtin_fma(hh, k1, x);
-      const double k2 = deriv(s, xs);
-      acc = __builtin_fma(2.0, k2, acc);
-      xs = __builtin_fma(hh, k2, x);
-      const double k3 = deriv(s, xs);
-      acc = __builtin_fma(2.0, k3, acc);
-      xs = __builtin_fma(h, k3, x);
-      const double k4 = deriv(s, xs);
-      x = __builtin_fma(h6, acc + k4, x);
-      if (INJ == 1) x = x + (e0 * w0 + e1 * w1);
-      bm = fmin(bm, row_margin(x));
-    };
-    float wcur[2 * U], wnext[2 * U];
-    load_group(0, wcur);
-    const int full = H / U;
-    int g = 0;
-    for (; g < full; ++g) {
-      load_group((g + 1) * U, wnext);
-#pragma unroll
-      for (int u = 0; u < U; ++u) step(wcur[2 * u], wcur[2 * u + 1]);
-#pragma unroll
-      for (int u = 0; u < 2 * U; ++u) wcur[u] = wnext[u];
-      if (a.early) {
-        if (quad_min64(bm) < 0.0) {
-          ++g;
-          break;
-        }
-        if ((g & 7) == 7 && qv == 0 &&
-            __hip_atomic_load(&S->fail64[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-          break;
-      }
-    }
-    if (g == full)
-      for (int u = 0; u < H - full * U; ++u) step(wcur[2 * u], wcur[2 * u + 1]);
-    double m = quad_min64(bm);
-    double bad = x - x;
-    bad = bad + dpp64<kSwap1>(bad);
-    bad = bad + dpp64<kSwap2>(bad);
-    if (!(bad == 0.0) || m != m) m = -INFINITY;
-    if (q == 0) {
+    } stop{refused, a.early, qv, 0, skip};
+    MxLane<RNG, INJ> M;
+    M.init(mc, S->v[c], a.h, a.hh, a.h6);
+    double x = a.st->x[q], bm;
+    int jq;
+    mx_rollout<RNG, INJ, 0>(M, a, t, k, x, bm, jq, stop);
+    double m = mx_min(bm);
+    const bool bad = (mx_scenarios(!(x - x == 0.0)) >> (lane & 15)) & 1u;
+    if (bad || m != m) m = -INFINITY;
+    if (q == 0 && live && !skip) {
       atomicMin(&S->key64[c], ord64(m));
       if (qv > 0) {
         a.per_key[(size_t)c * a.N + k] = ord64(m);
@@ -3210,51 +2932,6 @@ __global__ void k_equilibrium(const CtlArgs<KIND> a, double v, double* out) {
 // ---------------------------------------------------------------------------
 // Host-side argument filling and launchers
 // ---------------------------------------------------------------------------
-template <int KIND, class T>
-static RollArgs<KIND, T> make_args(const Problem& pr, double band, int early, int record,
-                                   const DevBuffers& b) {
-  using P = Plant<KIND, T>;
-  RollArgs<KIND, T> a;
-  memset(&a, 0, sizeof(a));
-  P::load(a.pc, pr.p.coeffs);
-  for (int r = 0; r < kNC; ++r) {
-    for (int i = 0; i < P::ny; ++i) a.F[r * P::ny + i] = (T)pr.c.F[r * P::ny + i];
-    a.g[r] = (T)pr.c.g[r];
-  }
-  a.h = (T)pr.dt;
-  a.hh = (T)(pr.dt * 0.5);
-  a.h6 = (T)(pr.dt / 6.0);
-  a.band = (T)band;
-  a.H = pr.H;
-  a.N = pr.s.N;
-  a.early = early;
-  a.record = record;
-  a.inject = pr.s.inject;
-  a.seed = pr.s.seed;
-  a.inst = pr.s.instance;
-  for (int c = 0; c < P::nw; ++c) {
-    a.wlo[c] = (float)pr.s.wlo[c];
-    a.wspan[c] = (float)(pr.s.whi[c] - pr.s.wlo[c]);
-  }
-  a.thlo = (float)(1.0 - pr.s.theta_rel);
-  a.thspan = (float)(2.0 * pr.s.theta_rel);
-  a.wbuf = b.wbuf;
-  a.thbuf = b.thbuf;
-  a.ring = b.ring;
-  for (int j = 0; j < kPairs; ++j) {
-    a.wring[j] = b.wpair[j];
-    a.thring[j] = b.thpair[j];
-  }
-  a.st = b.st;
-  a.srch = b.srch;
-  a.per_m = b.per_m;
-  a.per_j = b.per_j;
-  a.per_key = b.per_key;
-  a.rlist = b.rlist;
-  a.tan_dv = b.tan_dv;
-  return a;
-}
-
 template <int KIND>
 static CtlArgs<KIND> make_ctl(const Problem& pr, const DevBuffers& b, int closed_loop) {
   CtlArgs<KIND> a;
@@ -3267,22 +2944,6 @@ static CtlArgs<KIND> make_ctl(const Problem& pr, const DevBuffers& b, int closed
   a.grad = b.grad;
   return a;
 }
-
-template <int V>
-using IC = std::integral_constant<int, V>;
-
-template <class F>
-static hipError_t by_kind(int kind, F&& f) {
-  if (kind == 1) return f(IC<1>{});
-  if (kind == 2) return f(IC<2>{});
-  return hipErrorInvalidValue;
-}
-template <class F>
-static hipError_t by_bit(int v, F&& f) {
-  return v ? f(IC<1>{}) : f(IC<0>{});
-}
-
-static int div_up(size_t a, size_t b) { return (int)((a + b - 1) / b); }
 
 hipError_t launch_gen(const Problem& pr, const DevBuffers& b, hipStream_t st, uint32_t t_ofs) {
   return by_kind(pr.p.kind, [&](auto kc) {
@@ -3436,6 +3097,11 @@ hipError_t launch_rollout(const Problem& pr, double band, int precision, int ear
       });
     });
   }
+  if (precision == 1 && pr.p.kind == 1)  // 4-state plant in FP64: matrix cores
+    return launch_rollout_lq4_mx(
+        pr, 0.0, early_exit, record, cfg, b, st,
+        gen_rows_for((size_t)div_up((size_t)pr.s.N * 4, (size_t)cfg.block) * cfg.block), gen_w,
+        gen_th);
   const int gx = div_up((size_t)pr.s.N, (size_t)cfg.block);
   const dim3 grid(gx, cfg.cmax_round + gen_rows_for((size_t)gx * cfg.block));
   return by_kind(pr.p.kind, [&](auto kc) {
@@ -3458,7 +3124,7 @@ hipError_t launch_rollout(const Problem& pr, double band, int precision, int ear
             hipLaunchKernelGGL((k_rollout<K, float, R, I, 1>), grid, dim3(cfg.block), 0, st, a);
           else
             hipLaunchKernelGGL((k_rollout<K, float, R, I, 0>), grid, dim3(cfg.block), 0, st, a);
-        } else {
+        } else if constexpr (K == 2) {
           auto a = make_args<K, double>(pr, 0.0, early_exit, record, b);
           set_gen(a);
           if (cfg.chance)
@@ -3472,52 +3138,21 @@ hipError_t launch_rollout(const Problem& pr, double band, int precision, int ear
   });
 }
 
-// The FP64 counterpart of make_quad_coef (same slot layout).
-static QuadCoef64 make_quad_coef64(const Problem& pr) {
-  QuadCoef64 qc;
-  memset(&qc, 0, sizeof(qc));
-  const double* A = pr.p.coeffs;
-  const double* B = pr.p.coeffs + 16;
-  const double* G = pr.p.coeffs + 20;
-  const double* E = pr.p.coeffs + 36;
-  const double* Cm = pr.p.coeffs + 44;
-  double D[4][4];
-  for (int r = 0; r < 4; ++r)
-    for (int i = 0; i < 4; ++i) {
-      double acc = 0.0;
-      for (int y = 0; y < 2; ++y) acc += pr.c.F[r * 2 + y] * Cm[y * 4 + i];
-      D[r][i] = acc;
-    }
-  for (int q = 0; q < 4; ++q) {
-    for (int s = 0; s < 4; ++s) {
-      const int row = q ^ s;
-      qc.a[q][s] = A[row * 4 + q];
-      qc.g[q][s] = G[row * 4 + q];
-      qc.d[q][s] = -D[row][q];
-    }
-    qc.b[q] = B[q];
-    qc.e[q][0] = E[q * 2 + 0];
-    qc.e[q][1] = E[q * 2 + 1];
-    qc.grow[q] = pr.c.g[q];
-  }
-  return qc;
-}
-
 hipError_t launch_recheck(const Problem& pr, int early_exit, const LaunchCfg& cfg,
                           const DevBuffers& b, hipStream_t st, int decide) {
   const size_t cap = (size_t)cfg.cmax_round * pr.s.N;
   // Few workgroups: each of them counts itself on one device-scope counter at
   // the end (the last one decides), and near-band entries are rare; a
   // grid-stride loop takes any excess.
-  if (cfg.lanes == 4 && pr.p.kind == 1 && quad_draws_addressable(pr)) {
-    const int qblocks = div_up((cap < 4096 ? cap : 4096) * 4, 256);
-    const QuadCoef64 qc = make_quad_coef64(pr);
+  if (pr.p.kind == 1) {
+    const int mblocks = div_up(cap < 4096 ? cap : 4096, 64);
+    const MxCoef mc = make_mx_coef(pr);
     auto a = make_args<1, double>(pr, 0.0, early_exit, 0, b);
     return by_bit(pr.s.rng_mode, [&](auto rc) {
       constexpr int R = decltype(rc)::value;
       return by_bit(pr.s.inject, [&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        hipLaunchKernelGGL((k_recheck_lq4_quad<R, I>), dim3(qblocks), dim3(256), 0, st, a, qc,
+        hipLaunchKernelGGL((k_recheck_lq4_mx<R, I>), dim3(mblocks), dim3(256), 0, st, a, mc,
                            make_ctl<1>(pr, b, 0), decide);
         return hipGetLastError();
       });
@@ -3525,19 +3160,15 @@ hipError_t launch_recheck(const Problem& pr, int early_exit, const LaunchCfg& cf
   }
   // 9-state plant: up to one group of 16 lanes per possible entry (four per
   // workgroup, at most 256 workgroups), for the cooperative FP64 rollout
-  const int blocks = pr.p.kind == 2 ? (int)(div_up(cap, 4) < 256 ? div_up(cap, 4) : 256)
-                                    : (int)div_up(cap < 16384 ? cap : 16384, 64);
-  return by_kind(pr.p.kind, [&](auto kc) {
-    constexpr int K = decltype(kc)::value;
-    return by_bit(pr.s.rng_mode, [&](auto rc) {
-      constexpr int R = decltype(rc)::value;
-      return by_bit(pr.s.inject, [&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        auto a = make_args<K, double>(pr, 0.0, early_exit, 0, b);
-        hipLaunchKernelGGL((k_recheck<K, R, I>), dim3(blocks), dim3(64), 0, st, a,
-                           make_ctl<K>(pr, b, 0), decide);
-        return hipGetLastError();
-      });
+  const int blocks = (int)(div_up(cap, 4) < 256 ? div_up(cap, 4) : 256);
+  return by_bit(pr.s.rng_mode, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    return by_bit(pr.s.inject, [&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      auto a = make_args<2, double>(pr, 0.0, early_exit, 0, b);
+      hipLaunchKernelGGL((k_recheck<2, R, I>), dim3(blocks), dim3(64), 0, st, a,
+                         make_ctl<2>(pr, b, 0), decide);
+      return hipGetLastError();
     });
   });
 }
