@@ -113,6 +113,28 @@ __device__ __forceinline__ float t_tanh_shift(float x, float nk) {
   const float r = __builtin_amdgcn_rcpf(e + 1.0f);
   return __builtin_fmaf(-2.0f, r, 1.0f);
 }
+// tanh(x - xbar) - 1 = 1 / (-(1 + e^{2(x - xbar)}) / 2): the sum and the factor
+// are one fma, so the 9-state derivative (which adds the constant row sums of
+// its coupling matrix to the step forcing instead) saves the last operation.
+__device__ __forceinline__ float t_tanh_m1(float x, float nk) {
+  const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(2.8853900817779268f, x, nk));
+  return __builtin_amdgcn_rcpf(__builtin_fmaf(-0.5f, e, -0.5f));
+}
+// n / d for d normal and finite and a quotient in the normal range: reciprocal,
+// two Newton steps, and the residual's correction, the sequence of the compiler's
+// division without its scaling of extreme operands.
+__device__ __forceinline__ double t_div(double n, double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  r = fma(fma(-d, r, 1.0), r, r);
+  const double q = n * r;
+  return fma(fma(-d, q, n), r, q);
+}
+__device__ __forceinline__ float t_div(float n, float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float q = n * r;
+  return __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
+}
 // FP64 tanh of the FP64 rollouts and steady-state solves (written here, not
 // the library's): tanh|z| = t / (t + 2) with t = expm1(2|z|), which has no
 // cancellation at small |z|, carrying the sign of z; 1 once 2|z| >= 40 (then
@@ -123,12 +145,12 @@ __device__ __forceinline__ float t_tanh_shift(float x, float nk) {
 // its tail evaluated in Estrin's scheme (dependent depth 6 instead of Horner's
 // 12: the FP64 rechecks are bound by this latency); then
 // expm1(x) = 2^k expm1(r) + (2^k - 1).
-// Branch-free: arguments at or beyond 40 (and NaN) run the same arithmetic on
-// 40 and are replaced at the end.  Within 3 ulp of tanh over the arguments the
+// Branch-free: arguments at or beyond 40 run the same arithmetic on 40, where
+// the quotient rounds to 1; NaN stays NaN.  Within 3 ulp of tanh over the arguments the
 // rollouts meet (checked against an extended-precision reference in the tests).
 __device__ __forceinline__ double t_tanh(double z) {
   const double ax = 2.0 * fabs(z);
-  const double x = fmin(ax, 40.0);
+  const double x = ax > 40.0 ? 40.0 : ax;
   constexpr double kLn2Head = 0x1.62e42ff0p-1;         // ln 2 to 32 significant bits
   constexpr double kLn2Tail = -0x1.718432a1b0e26p-35;  // ln 2 - kLn2Head
   constexpr double kInvLn2 = 0x1.71547652b82fep+0;
@@ -153,12 +175,24 @@ __device__ __forceinline__ double t_tanh(double z) {
   const double em = p * r;  // expm1(r)
   const double two_k = ldexp(1.0, (int)k);
   const double t = fma(two_k, em, two_k - 1.0);
-  const double th = copysign(t / (t + 2.0), z);
-  const double sat = ax == ax ? copysign(1.0, z) : z;
-  return ax < 40.0 ? th : sat;
+  return copysign(t_div(t, t + 2.0), z);
 }
 __device__ __forceinline__ float t_sqrt(float z) { return __builtin_amdgcn_sqrtf(z); }
-__device__ __forceinline__ double t_sqrt(double z) { return sqrt(z); }
+// FP64 square root of z >= 0: reciprocal square root, one coupled Newton step
+// and two residual corrections.  Below 2^-960 (where the compiler's sqrt scales
+// its operand) the result is 0, an absolute error of at most 2^-480.
+__device__ __forceinline__ double t_sqrt(double z) {
+  const double y = __builtin_amdgcn_rsq(z);
+  double g = z * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, z), h, g);
+  g = fma(fma(-g, g, z), h, g);
+  return z < 0x1p-960 ? 0.0 : g;
+}
+__device__ __forceinline__ float t_min(float a, float b) { return fminf(a, b); }
+__device__ __forceinline__ double t_min(double a, double b) { return fmin(a, b); }
 __device__ __forceinline__ float t_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double t_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -302,12 +336,16 @@ struct Plant<2, T> {
     T W[81], xbar[9], thnom[20];
     T c_q0, p_amb, d0, d1, p1ref;
     T nkxbar[9];  // -2 log2(e) xbar (FP32 tanh with the shift in its exponent)
+    T csum[9];    // FP32: row sums of W (the derivative sums W (tanh - 1)); FP64: 0
   };
   struct Lane {
     T a[9], kq[6], b[3], mu[2];
     T v;
-    T axb[9];    // a_i xbar_i: -a_i (x_i - xbar_i) = -a_i x_i + a_i xbar_i, the constant
-                 // part carried in the step forcing s_i
+    T axb[9];    // what the step forcing s_i carries besides w_i: a_i xbar_i (the
+                 // derivative takes -a_i x_i for -a_i (x_i - xbar_i)), csum_i and the
+                 // constant terms of phi_7 and phi_9
+    T a9;        // a_9 + mu_2 v: phi_9 is linear in x_9
+    T b2v;       // b_2 v
     const T* W;  // the coupling matrix the derivative reads (c.W, or a copy in registers)
   };
   __host__ __device__ static const T* nominal_theta(const Coef& c) { return c.thnom; }
@@ -321,6 +359,11 @@ struct Plant<2, T> {
     c.d1 = (T)s[113];
     c.p1ref = (T)s[114];
     for (int i = 0; i < 9; ++i) c.nkxbar[i] = (T)(-2.8853900817779268 * s[81 + i]);
+    for (int i = 0; i < 9; ++i) {
+      double sum = 0.0;
+      for (int j = 0; j < 9; ++j) sum += s[9 * i + j];
+      c.csum[i] = sizeof(T) == 4 ? (T)sum : (T)0;
+    }
   }
   __device__ static void lane_init(const Coef& c, const T* th, T v, Lane& L) {
 #pragma unroll
@@ -333,11 +376,14 @@ struct Plant<2, T> {
     L.mu[1] = th[19];
     L.v = v;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) L.axb[i] = L.a[i] * c.xbar[i];
+    for (int i = 0; i < 9; ++i) L.axb[i] = t_fma(L.a[i], c.xbar[i], c.csum[i]);
+    L.axb[6] = t_fma(L.b[0], v, L.axb[6]);
+    L.axb[8] = t_fma(L.b[2] + L.mu[1], v, L.axb[8]);
+    L.a9 = t_fma(L.mu[1], v, L.a[8]);
+    L.b2v = L.b[1] * v;
     L.W = c.W;
   }
-  // Step forcing of component i: w_i + a_i xbar_i (the derivative takes
-  // -a_i x_i, so the sum is w_i - a_i (x_i - xbar_i))
+  // Step forcing of component i: w_i and the constant terms
   __device__ static void force(const Coef&, const Lane& L, const T* w, T* s) {
 #pragma unroll
     for (int i = 0; i < 9; ++i) s[i] = w[i] + L.axb[i];
@@ -351,34 +397,24 @@ struct Plant<2, T> {
     if constexpr (sizeof(T) == 4) return t_tanh_shift(x, nkxbar);
     else return t_tanh(x - xbar);
   }
-  // Component i of the derivative from the pieces of the evaluation point:
-  // x_i (si carries a_i xbar_i), the vector tz = tanh(x - xbar), the orifice
-  // flows q_i = qa qb and q_{i+1} = qk qr as factor pairs (i < 6), and the
-  // states x0, x6, x8.  Every
-  // product-sum is an explicit fma and nothing here is contracted, so the
-  // one-lane derivative below and the FP64 recheck that gives each component
-  // its own lane round alike.
-  __device__ static T comp(int i, T ai, const T* wrow, T si, T xi, const T* tz, T qa, T qb,
-                           T qk, T qr, T x0, T x6, T x8, const Lane& L, T p1ref) {
+  // What the coupling matrix multiplies: FP32 tanh - 1 (its row sums are in the
+  // step forcing), FP64 tanh.
+  __device__ static T act(T x, T xbar, T nkxbar) {
+    if constexpr (sizeof(T) == 4) return t_tanh_m1(x, nkxbar);
+    else return t_tanh(x - xbar);
+  }
+  // Row i of the derivative: s_i - K R - A x_i + W_i . act + P Q, one fma per
+  // term in this order, nothing contracted, so that the one-lane derivative and
+  // the lane groups (one lane per row) round alike.  The terms per row:
+  //   i < 6:  K R = k_i r_i (the flow out), P Q = c_q0 x_7 (i = 0) or the flow in
+  //   i = 6:  P Q = -(mu_1 x_7) (x_1 - p1ref);  i = 7: b_2 v x_7;  i = 8: none
+  __device__ static T row(T s, T K, T R, T A, T xi, const T* wrow, const T* act, T Pq, T Q) {
 #pragma clang fp contract(off)
-    // phi_i = A B + C D in one form for every row (i < 6: q_i - q_{i+1};
-    // 6: b1 v - mu1 w1 (p1 - p1ref); 7: b2 v w1; 8: b3 v - mu2 (w3 - 1) v);
-    // every candidate is computed and then selected (no branch where i varies
-    // over the lanes).  The sum runs s_i + C D, - a_i x_i, the coupling
-    // terms, + A B: one fma per term.
-    const T a6 = -(L.mu[0] * x6), b6 = x0 - p1ref;
-    const T a7 = L.b[1] * L.v;
-    const T a8 = -(L.mu[1] * (x8 - (T)1));
-    const bool lo = i < 6, r6 = i == 6, r7 = i == 7;
-    const T A = lo ? qa : (r6 ? a6 : (r7 ? a7 : a8));
-    const T B = lo ? qb : (r6 ? b6 : (r7 ? x6 : L.v));
-    const T C = lo ? -qk : (r6 ? L.b[0] : L.b[2]);
-    const T D = lo ? qr : L.v;
-    T a = r7 ? si : t_fma(C, D, si);
-    a = t_fma(-ai, xi, a);
+    T a = t_fma(-K, R, s);
+    a = t_fma(-A, xi, a);
 #pragma unroll
-    for (int j = 0; j < 9; ++j) a = t_fma(wrow[j], tz[j], a);
-    return t_fma(A, B, a);
+    for (int j = 0; j < 9; ++j) a = t_fma(wrow[j], act[j], a);
+    return t_fma(Pq, Q, a);
   }
   // Square-root factor of the orifice flow q_{l+1}: sqrt(max(p_l - p_{l+1}, 0))
   // with p_7 = p_amb.
@@ -387,19 +423,24 @@ struct Plant<2, T> {
     return t_sqrt(dp > (T)0 ? dp : (T)0);
   }
   __device__ static void deriv(const Coef& c, const Lane& L, const T* s, const T* x, T* xd) {
+#pragma clang fp contract(off)
     T tz[9], r[6];
 #pragma unroll
-    for (int j = 0; j < 9; ++j) tz[j] = tanh_at(x[j], c.xbar[j], c.nkxbar[j]);
+    for (int j = 0; j < 9; ++j) tz[j] = act(x[j], c.xbar[j], c.nkxbar[j]);
 #pragma unroll
     for (int l = 0; l < 6; ++l) r[l] = orifice(x[l], (l < 5) ? x[l + 1] : c.p_amb);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-      const T qa = i == 0 ? c.c_q0 : (i < 6 ? L.kq[i > 0 ? i - 1 : 0] : (T)0);
-      const T qb = i == 0 ? x[6] : (i < 6 ? r[i > 0 ? i - 1 : 0] : (T)0);
-      const T qk = i < 6 ? L.kq[i < 6 ? i : 0] : (T)0;
-      const T qr = i < 6 ? r[i < 6 ? i : 0] : (T)0;
-      xd[i] = comp(i, L.a[i], &L.W[9 * i], s[i], x[i], tz, qa, qb, qk, qr, x[0], x[6], x[8], L,
-                   c.p1ref);
+      T a = s[i];
+      if (i < 6) a = t_fma(-L.kq[i < 6 ? i : 0], r[i < 6 ? i : 0], a);
+      a = t_fma(-(i < 8 ? L.a[i] : L.a9), x[i], a);
+#pragma unroll
+      for (int j = 0; j < 9; ++j) a = t_fma(L.W[9 * i + j], tz[j], a);
+      if (i == 0) a = t_fma(c.c_q0, x[6], a);
+      else if (i < 6) a = t_fma(L.kq[i - 1], r[i - 1], a);
+      else if (i == 6) a = t_fma(-(L.mu[0] * x[6]), x[0] - c.p1ref, a);
+      else if (i == 7) a = t_fma(L.b2v, x[6], a);
+      xd[i] = a;
     }
   }
   __device__ static void post(const Coef&, const T* w, T* x) {
@@ -407,7 +448,7 @@ struct Plant<2, T> {
     for (int i = 0; i < 9; ++i) x[i] = x[i] + w[i];
   }
   __device__ static void output(const Coef& c, const Lane&, const T* x, T* y) {
-    y[0] = c.c_q0 * x[6] / t_fma(c.d1, x[8], c.d0);
+    y[0] = t_div(c.c_q0 * x[6], t_fma(c.d1, x[8], c.d0));
     y[1] = x[0];
     y[2] = x[6];
   }
@@ -676,6 +717,14 @@ __device__ __forceinline__ void rk4_vjp(const typename Plant<KIND, T>::Coef& c,
 }
 
 // Margin over kNC padded rows (padding rows: F = 0, g = +inf).
+template <int NY, class T>
+__device__ __forceinline__ T margin_row(const T* F, const T* g, const T* y, int r) {
+  T m = g[r];
+#pragma unroll
+  for (int i = 0; i < NY; ++i) m = t_fma(-F[r * NY + i], y[i], m);
+  return m;
+}
+
 // Margin and its minimising row.
 template <int NY, class T>
 __device__ __forceinline__ T margin_rows_arg(const T* F, const T* g, const T* y, int& rarg) {
@@ -683,10 +732,7 @@ __device__ __forceinline__ T margin_rows_arg(const T* F, const T* g, const T* y,
   rarg = 0;
 #pragma unroll
   for (int r = 0; r < kNC; ++r) {
-    T fy = F[r * NY] * y[0];
-#pragma unroll
-    for (int i = 1; i < NY; ++i) fy = t_fma(F[r * NY + i], y[i], fy);
-    const T m = g[r] - fy;
+    const T m = margin_row<NY>(F, g, y, r);
     if (m < best || m != m) {
       best = m;
       rarg = r;
@@ -695,18 +741,18 @@ __device__ __forceinline__ T margin_rows_arg(const T* F, const T* g, const T* y,
   return best;
 }
 
+// NaN if any row is NaN (the caller maps it to -inf): the minimum ignores NaN
+// rows, and the sum of the rows is NaN exactly when one of them is, or when one
+// is -inf beside a +inf padding row.
 template <int NY, class T>
 __device__ __forceinline__ T margin_rows(const T* F, const T* g, const T* y) {
-  T best = t_inf<T>();
+  static_assert(kNC == 4, "four rows");
+  T m[kNC];
 #pragma unroll
-  for (int r = 0; r < kNC; ++r) {
-    T fy = F[r * NY] * y[0];
-#pragma unroll
-    for (int i = 1; i < NY; ++i) fy = t_fma(F[r * NY + i], y[i], fy);
-    const T m = g[r] - fy;
-    best = (m < best || m != m) ? m : best;  // a NaN row stays NaN (caller maps it to -inf)
-  }
-  return best;
+  for (int r = 0; r < kNC; ++r) m[r] = margin_row<NY>(F, g, y, r);
+  const T sum = (m[0] + m[1]) + (m[2] + m[3]);
+  const T best = t_min(t_min(m[0], m[1]), t_min(m[2], m[3]));
+  return sum == sum ? best : sum;
 }
 
 }  // namespace rg

@@ -1,0 +1,116 @@
+// Rollouts of the 9-state plant by groups of 9 lanes (rg_fc9_lanes.hpp): FP64
+// handles, and FP32 rounds with few scenario-candidate pairs.
+#include <hip/hip_runtime.h>
+
+#include "rg_fc9_lanes.hpp"
+
+namespace rg {
+
+// blockIdx.y = candidate, seven scenarios per wave.  The per-scenario
+// bookkeeping is that of the one-lane kernel, made by the group's first lane;
+// the margins equal that kernel's bit for bit.  CKPT = 1: the checkpoint
+// candidate's groups store the adjoint's checkpoints.  CHANCE = 1: the
+// chance-constrained verdict (groups stop on their own, every margin key kept).
+template <class T, int RNG, int INJ, int CKPT, int CHANCE>
+__global__ void __launch_bounds__(256) k_rollout_fc9_lanes(const RollArgs<2, T> a) {
+  if (gen_rows<2>(a)) return;
+  __shared__ unsigned long long sh[16];
+  __shared__ __align__(16) T xch[4 * kWaveSlots<T>];
+  DevSearch* S = a.srch;
+  const int c = blockIdx.y;
+  if (S->done || c >= S->n_cand) return;  // uniform over the workgroup
+  const bool ck = CKPT == 1 && c == (a.ckpt_cand >= 0 ? a.ckpt_cand : S->nk_idx);
+  const int early = a.early && !S->full[c];
+  if (refused_by_steady_state(early, S, c)) return;
+  const GroupLane gl;
+  const int wave = threadIdx.x >> 6;
+  const int k = (int)(blockIdx.x * (blockDim.x >> 6) + wave) * kWaveGroups + gl.grp;
+  const uint32_t t = a.st->t;
+  const int q = CHANCE ? S->q : 0;
+  const bool live = gl.grp < kWaveGroups && k < a.N;
+  T m = t_inf<T>();
+  int jb = 0, ns = 0;
+  if (live) {  // whole groups are active or inactive together
+    T* slot = xch + wave * kWaveSlots<T> + gl.grp * kGroupStride<T>;
+    bool stopped = false;  // the candidate died while this wave ran (no recheck needed)
+    if constexpr (CHANCE)
+      m = rollout_fc9_lanes<T, RNG, INJ, false, 0>(a, early, (T)S->v[c], k, t,
+                                                   early ? &S->dead[c] : nullptr, slot, gl, jb, ns);
+    else
+      m = rollout_fc9_lanes<T, RNG, INJ, true, CKPT>(a, early, (T)S->v[c], k, t, &S->dead[c], slot,
+                                                     gl, jb, ns, ck, &stopped);
+    if (gl.li == 0) {
+      if (CHANCE) a.per_key[(size_t)c * a.N + k] = ord64((double)m);
+      if (a.record) {
+        a.per_m[(size_t)c * a.N + k] = (float)m;
+        a.per_j[(size_t)c * a.N + k] = jb;
+      }
+      if (m < -a.band) {
+        if (q == 0 || atomicAdd(&S->nviol[c], 1) >= q)
+          __hip_atomic_store(&S->dead[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else if (m < a.band && !stopped) {
+        const int idx = atomicAdd(&S->n_recheck, 1);
+        a.rlist[idx] = make_int2(c, k);
+      }
+    }
+  }
+  const bool own = live && gl.li == 0;
+  const unsigned long long key = own ? lane_key(m, k) : ~0ull;
+  const unsigned long long kall = block_min_u64(key, sh);
+  const unsigned long long kfar = block_min_u64((own && m >= a.band) ? key : ~0ull, sh);
+  int wsum = own ? ns : 0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) wsum += __shfl_xor(wsum, off);
+  if ((threadIdx.x & 63) == 0) atomicAdd(&S->lane_steps, (unsigned long long)wsum);
+  if (threadIdx.x == 0) {
+    atomicMin(&S->key_all[c], kall);
+    if (kfar != ~0ull) atomicMin(&S->key_far[c], kfar);
+  }
+}
+
+hipError_t launch_rollout_fc9_lanes(const Problem& pr, double band, int precision, int early_exit,
+                                    int record, const LaunchCfg& cfg, const DevBuffers& b,
+                                    hipStream_t st, int ckpt_cand, int Kc, int gen_rows,
+                                    float* gen_w, float* gen_th) {
+  const int gx = div_up((size_t)pr.s.N, (size_t)fc9_lanes_per_block(cfg.block));
+  const dim3 grid(gx, cfg.cmax_round + gen_rows);
+  auto fill = [&](auto& a) {
+    a.ckpt = b.adj_ckpt;
+    a.Kc = Kc;
+    a.ckpt_cand = ckpt_cand;
+    if (gen_rows > 0) {
+      a.gen_row0 = cfg.cmax_round;
+      a.gen_ofs = kSpecMax + 1;
+      a.gen_w = gen_w;
+      a.gen_th = gen_th;
+    }
+  };
+  return by_bit(pr.s.rng_mode, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    return by_bit(pr.s.inject, [&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      if (precision == 0) {
+        auto a = make_args<2, float>(pr, band, early_exit, record, b);
+        fill(a);
+        if (ckpt_cand >= -1)
+          hipLaunchKernelGGL((k_rollout_fc9_lanes<float, R, I, 1, 0>), grid, dim3(cfg.block), 0, st,
+                             a);
+        else
+          hipLaunchKernelGGL((k_rollout_fc9_lanes<float, R, I, 0, 0>), grid, dim3(cfg.block), 0, st,
+                             a);
+      } else {
+        auto a = make_args<2, double>(pr, 0.0, early_exit, record, b);
+        fill(a);
+        if (cfg.chance)
+          hipLaunchKernelGGL((k_rollout_fc9_lanes<double, R, I, 0, 1>), grid, dim3(cfg.block), 0,
+                             st, a);
+        else
+          hipLaunchKernelGGL((k_rollout_fc9_lanes<double, R, I, 0, 0>), grid, dim3(cfg.block), 0,
+                             st, a);
+      }
+      return hipGetLastError();
+    });
+  });
+}
+
+}  // namespace rg

@@ -16,6 +16,7 @@
 // No step reads back to the host.  All search state lives in DevSearch.
 #include <hip/hip_runtime.h>
 
+#include "rg_fc9_lanes.hpp"
 #include "rg_lq4_mx.hpp"
 
 namespace rg {
@@ -210,242 +211,30 @@ __device__ __forceinline__ T rollout_lane(const A& a, int early, T v, int k, uin
   return best;
 }
 
-// ---------------------------------------------------------------------------
-// Rollout of one 9-state scenario by a group of 16 lanes (a DPP row), for the
-// FP64 recheck of a few near-band scenarios and for FP32 rounds with few
-// scenarios: one lane per scenario would leave every serial RK4 step on one
-// lane while most of the chip idles.  Lane i of the group owns state
-// component i; lanes 9..15 repeat component 8 and nothing reads them.  At every
-// derivative evaluation each lane computes its own tanh and orifice factors,
-// the group exchanges (x_i, tanh z_i) through its 16 LDS slots (the orifice
-// factors through DPP row shifts), and each lane forms its component with
-// Plant<2>::comp, the arithmetic of the one-lane rollout; every lane computes
-// the margin from the exchanged state.  The result equals that of
-// rollout_lane<2, T> bit for bit.  Control flow is uniform over the group
-// (over the wave with WAVE): every branch depends on exchanged values or on a
-// ballot.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void group_sync() {
-  // The group is part of one wave, whose LDS accesses complete in program
-  // order; this only keeps the compiler from moving them across.
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <class T>
-struct Pair;
-template <>
-struct Pair<float> {
-  using type = float2;
-};
-template <>
-struct Pair<double> {
-  using type = double2;
-};
-
-// WAVE (FP32 rollouts of one candidate): the whole wave stops at the first
-// violation of any of its groups, as rollout_lane's WAVE form, and stop_flag
-// is that candidate's dead flag; otherwise (FP64 rechecks) the group stops on
-// its own and stop_flag is only read.  CKPT with ck: checkpoints as
-// rollout_lane's (lane i stores component i).  jbest and nsteps as
-// rollout_lane's.
-template <class T, int RNG, int INJ, bool WAVE = false, int CKPT = 0>
-__device__ T rollout_fc9_group(const RollArgs<2, T>& a, int early, T v, int k, uint32_t t,
-                               int32_t* stop_flag, typename Pair<T>::type* xch, int li,
-                               unsigned long long gmask, int& jbest, int& nsteps, bool ck = false,
-                               bool* stopped = nullptr) {
-  using P = Plant<2, T>;
-  const int i = li < 9 ? li : 8;
-  T th[P::nth];
-  {
-    float f[P::nth];
-    if (RNG == 0) {
-      const float* tb = step_th(a, t);
-#pragma unroll
-      for (int c = 0; c < P::nth; ++c) f[c] = tb[(size_t)c * a.N + k];
-    } else {
-      draw_theta_factor<P::nth>(a.seed, a.inst, t, (uint32_t)k, a.thlo, a.thspan, f);
-    }
-#pragma unroll
-    for (int c = 0; c < P::nth; ++c) th[c] = a.pc.thnom[c] * (T)f[c];
-  }
-  typename P::Lane L;
-  P::lane_init(a.pc, th, v, L);
-  // this lane's coefficients: a_i, xbar_i (and its tanh exponent shift), a_i
-  // xbar_i, row i of W, k_{i-1} and k_i of the orifice flows q_i and q_{i+1},
-  // the draw bounds of w_i
-  T ai = L.a[0], xb = a.pc.xbar[0], nkxb = a.pc.nkxbar[0], axb = L.axb[0], kql = (T)0,
-    kqh = L.kq[0], wrow[9];
-  float wlo = a.wlo[0], wsp = a.wspan[0];
-#pragma unroll
-  for (int j = 0; j < 9; ++j) wrow[j] = a.pc.W[j];
-#pragma unroll
-  for (int r = 1; r < 9; ++r) {
-    const bool on = i == r;
-    ai = on ? L.a[r] : ai;
-    xb = on ? a.pc.xbar[r] : xb;
-    nkxb = on ? a.pc.nkxbar[r] : nkxb;
-    axb = on ? L.axb[r] : axb;
-    wlo = on ? a.wlo[r] : wlo;
-    wsp = on ? a.wspan[r] : wsp;
-#pragma unroll
-    for (int j = 0; j < 9; ++j) wrow[j] = on ? a.pc.W[9 * r + j] : wrow[j];
-    if (r < 6) kqh = on ? L.kq[r] : kqh;
-    if (r < 6) kql = on ? L.kq[r - 1] : kql;
-  }
-  // exchange of the evaluation point: X and TZ receive (x_j, tanh z_j) of
-  // every component; rh = r_i and rl = r_{i-1}, the orifice factors of q_{i+1}
-  // and q_i, come from the neighbouring lanes by DPP row shifts
-  T X[9], TZ[9], rl, rh;
-  auto exch = [&](T xv) {
-    const T xn = dpp_row<0x101>(xv);  // row_shl:1, x_{i+1}
-    rh = P::orifice(xv, i < 5 ? xn : a.pc.p_amb);
-    rl = dpp_row<0x111>(rh);  // row_shr:1, r_{i-1}
-    typename Pair<T>::type e;
-    e.x = xv;
-    e.y = P::tanh_at(xv, xb, nkxb);
-    xch[li] = e;
-    group_sync();
-#pragma unroll
-    for (int j = 0; j < 9; ++j) {
-      const typename Pair<T>::type f = xch[j];
-      X[j] = f.x;
-      TZ[j] = f.y;
-    }
-    group_sync();
-  };
-  // component i of the derivative at the exchanged point (own component xv)
-  auto eval = [&](T xv, T si) {
-    const T qa = i == 0 ? a.pc.c_q0 : kql;
-    const T qb = i == 0 ? X[6] : rl;
-    return P::comp(i, ai, wrow, si, xv, TZ, qa, qb, kqh, rh, X[0], X[6], X[8], L, a.pc.p1ref);
-  };
-  const float* wb = RNG == 0 ? step_w(a, t) : nullptr;
-  const int wq = i & 3;
-  auto load = [&](int j) -> float {
-    if (RNG == 0) return wb[((size_t)j * P::nw + i) * a.N + k];
-    const Words r = philox10((uint32_t)k, (uint32_t)j, t, (uint32_t)(i >> 2), a.seed, a.inst);
-    const uint32_t word = wq == 0 ? r.v[0] : (wq == 1 ? r.v[1] : (wq == 2 ? r.v[2] : r.v[3]));
-    return box_draw(word, wlo, wsp);
-  };
-  T xv = (T)a.st->x[i];
-  exch(xv);
-  T y[P::ny];
-  P::output(a.pc, L, X, y);
-  T best = margin_rows<P::ny>(a.F, a.g, y);
-  if (best != best) best = -t_inf<T>();
-  jbest = 0;
-  int ck_left = 0, ck_seg = 0;  // steps to the next checkpoint, its index
-  if constexpr (CKPT) {
-    if (ck) {
-      if (li < 9) a.ckpt[(size_t)i * a.N + k] = (float)xv;
-      ck_left = a.Kc;
-    }
-  }
-  float wc = a.H > 0 ? load(0) : 0.0f, wn = 0.0f;
-  int j = 0;
-  bool stop_seen = false;  // dead flag read at the start of an 8-step block, tested at its end
-  for (; j < a.H; ++j) {
-    if (j + 1 < a.H) wn = load(j + 1);
-    if (WAVE && early && (j & 7) == 0)
-      stop_seen = __hip_atomic_load(stop_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    const T si = INJ == 0 ? (T)wc + axb : axb;  // P::force / P::force0 of component i
-    T kk = eval(xv, si);
-    T acc = kk;
-    T xs = t_fma(a.hh, kk, xv);
-    exch(xs);
-    kk = eval(xs, si);
-    acc = t_fma((T)2, kk, acc);
-    xs = t_fma(a.hh, kk, xv);
-    exch(xs);
-    kk = eval(xs, si);
-    acc = t_fma((T)2, kk, acc);
-    xs = t_fma(a.h, kk, xv);
-    exch(xs);
-    kk = eval(xs, si);
-    xv = t_fma(a.h6, acc + kk, xv);
-    if (INJ == 1) xv = xv + (T)wc;
-    exch(xv);
-    P::output(a.pc, L, X, y);
-    T m = margin_rows<P::ny>(a.F, a.g, y);
-    m = (m == m) ? m : -t_inf<T>();
-    if (m < best) {
-      best = m;
-      jbest = j + 1;
-    }
-    if constexpr (CKPT) {
-      if (ck && --ck_left == 0) {
-        ck_left = a.Kc;
-        ++ck_seg;
-        if (li < 9) a.ckpt[((size_t)ck_seg * P::n + i) * a.N + k] = (float)xv;
-      }
-    }
-    if (early) {
-      if constexpr (WAVE) {
-        // every group of the wave evaluates the same candidate
-        const bool viol = best < -a.band;
-        if (__builtin_amdgcn_ballot_w64(viol) != 0) {
-          if (viol && li == 0)
-            __hip_atomic_store(stop_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          *stopped = true;
-          ++j;
-          break;
-        }
-        if ((j & 7) == 7 && __builtin_amdgcn_ballot_w64(stop_seen) != 0) {
-          *stopped = true;
-          ++j;
-          break;
-        }
-      } else {
-        if (best < -a.band) {
-          ++j;
-          break;
-        }
-        if ((j & 31) == 31 && stop_flag) {
-          const bool f =
-              __hip_atomic_load(stop_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-          if (__builtin_amdgcn_ballot_w64(f) & gmask) {
-            ++j;
-            break;
-          }
-        }
-      }
-    }
-    wc = wn;
-  }
-  nsteps = j;
-  bool finite = true;
-#pragma unroll
-  for (int jj = 0; jj < 9; ++jj) finite = finite && (X[jj] - X[jj] == (T)0);
-  if (!finite) best = -t_inf<T>();
-  return best;
-}
-
 // The FP64 recheck of near-band entries [g0, n) with stride gstride over
-// groups of 16 lanes (rollout_fc9_group), with the verdict updates of
-// k_recheck made by the group's first lane.  blockDim.x is a multiple of 16
-// and at most 64.
+// groups of 9 lanes (rollout_fc9_lanes), with the verdict updates of k_recheck
+// made by the group's first lane.  Lane 63 of each wave (no group) passes by.
 template <int RNG, int INJ>
-__device__ void recheck_fc9_groups(const RollArgs<2, double>& a, DevSearch* S, int n, uint32_t t,
-                                   int g0, int gstride) {
-  __shared__ double2 xch[64];
-  const int li = threadIdx.x & 15;
-  double2* slot = xch + (threadIdx.x & ~15);
-  const unsigned long long gmask = 0xffffull << (threadIdx.x & 48);
+__device__ void recheck_fc9_lanes(const RollArgs<2, double>& a, DevSearch* S, int n, uint32_t t,
+                                  const GroupLane& gl, double* slot, int g0, int gstride) {
   const int q = S->q;
+  if (gl.grp >= kWaveGroups) return;
   for (int e = g0; e < n; e += gstride) {
     const int2 en = a.rlist[e];
     const int c = en.x, k = en.y;
+    // The verdict needs one failing entry only, also for a candidate whose FP32
+    // rollout ran in full (the Newton iterate): its rechecks stop at the first
+    // FP64 violation too.
     const bool skip =
         a.early && (__hip_atomic_load(&S->dead[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
                     __hip_atomic_load(&S->fail64[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    if (__builtin_amdgcn_ballot_w64(skip) & gmask) continue;
+    if (__builtin_amdgcn_ballot_w64(skip) & gl.mask) continue;
     int jb = 0, ns = 0;
-    const double m = rollout_fc9_group<double, RNG, INJ>(
-        a, a.early, S->v[c], k, t, a.early && q == 0 ? &S->fail64[c] : nullptr, slot, li, gmask,
-        jb, ns);
-    if (li != 0) continue;
+    // chance-constrained verdict: one FP64 violation refuses the candidate only
+    // once more than q scenarios violate, so an entry does not stop on another's
+    const double m = rollout_fc9_lanes<double, RNG, INJ>(
+        a, a.early, S->v[c], k, t, a.early && q == 0 ? &S->fail64[c] : nullptr, slot, gl, jb, ns);
+    if (gl.li != 0) continue;
     atomicMin(&S->key64[c], ord64(m));
     if (q > 0) {
       a.per_key[(size_t)c * a.N + k] = ord64(m);
@@ -627,60 +416,6 @@ __global__ void __launch_bounds__(256) k_rollout(const RollArgs<KIND, T> a) {
   if (gen_rows<KIND>(a)) return;
   __shared__ unsigned long long sh[16];
   rollout_block<KIND, T, RNG, INJ, CKPT, CHANCE>(a, blockIdx.y, blockIdx.x, sh);
-}
-
-// 9-state FP32 rollouts with one scenario per group of 16 lanes
-// (rollout_fc9_group), robust verdict: blockIdx.y = candidate, 16 scenarios
-// per 256 lanes.  The per-scenario bookkeeping is rollout_block's, made by the
-// group's first lane; the margins equal the one-lane kernel's bit for bit.
-// CKPT = 1: the checkpoint candidate's groups store the adjoint's checkpoints.
-template <int RNG, int INJ, int CKPT>
-__global__ void __launch_bounds__(256) k_rollout_fc9_group(const RollArgs<2, float> a) {
-  if (gen_rows<2>(a)) return;
-  __shared__ unsigned long long sh[16];
-  __shared__ float2 xch[256];
-  DevSearch* S = a.srch;
-  const int c = blockIdx.y;
-  if (S->done || c >= S->n_cand) return;  // uniform over the workgroup
-  const bool ck = CKPT == 1 && c == (a.ckpt_cand >= 0 ? a.ckpt_cand : S->nk_idx);
-  const int early = a.early && !S->full[c];
-  if (refused_by_steady_state(early, S, c)) return;
-  const int li = threadIdx.x & 15;
-  const int k = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 4);
-  const unsigned long long gmask = 0xffffull << (threadIdx.x & 48);
-  const uint32_t t = a.st->t;
-  float m = INFINITY;
-  int jb = 0, ns = 0;
-  if (k < a.N) {  // whole groups are active or inactive together
-    bool stopped = false;  // the candidate died while this wave ran (no recheck needed)
-    m = rollout_fc9_group<float, RNG, INJ, true, CKPT>(a, early, (float)S->v[c], k, t, &S->dead[c],
-                                                       xch + (threadIdx.x & ~15u), li, gmask, jb,
-                                                       ns, ck, &stopped);
-    if (li == 0) {
-      if (a.record) {
-        a.per_m[(size_t)c * a.N + k] = m;
-        a.per_j[(size_t)c * a.N + k] = jb;
-      }
-      if (m < -a.band) {
-        __hip_atomic_store(&S->dead[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else if (m < a.band && !stopped) {
-        const int idx = atomicAdd(&S->n_recheck, 1);
-        a.rlist[idx] = make_int2(c, k);
-      }
-    }
-  }
-  const bool own = li == 0 && k < a.N;
-  const unsigned long long key = own ? lane_key(m, k) : ~0ull;
-  const unsigned long long kall = block_min_u64(key, sh);
-  const unsigned long long kfar = block_min_u64((own && m >= a.band) ? key : ~0ull, sh);
-  int wsum = li == 0 ? ns : 0;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) wsum += __shfl_xor(wsum, off);
-  if ((threadIdx.x & 63) == 0) atomicAdd(&S->lane_steps, (unsigned long long)wsum);
-  if (threadIdx.x == 0) {
-    atomicMin(&S->key_all[c], kall);
-    if (kfar != ~0ull) atomicMin(&S->key_far[c], kfar);
-  }
 }
 
 // Batched serving: one launch per search round covers every instance of a
@@ -1145,51 +880,20 @@ __global__ void __launch_bounds__(256, 2) k_recheck_lq4_mx(const RollArgs<1, dou
   if (decide) last_block_decides<1>(ctl);
 }
 
-// FP64 re-simulation of the near-band list.
-template <int KIND, int RNG, int INJ>
-__global__ void __launch_bounds__(64) k_recheck(const RollArgs<KIND, double> a,
-                                                const CtlArgs<KIND> ctl, int decide) {
+// FP64 re-simulation of the near-band list, 9-state plant (one entry per group
+// of 9 lanes).
+template <int RNG, int INJ>
+__global__ void __launch_bounds__(64) k_recheck_fc9(const RollArgs<2, double> a,
+                                                    const CtlArgs<2> ctl, int decide) {
+  __shared__ __align__(16) double xch[kWaveSlots<double>];
   DevSearch* S = a.srch;
   if (S->done) return;
-  const int n = S->n_recheck;
-  const uint32_t t = a.st->t;
-  if constexpr (KIND == 2) {
-    // up to two entries per group of 16 lanes: the cooperative rollout
-    const int groups = (int)(gridDim.x * blockDim.x) >> 4;
-    if (n <= 2 * groups) {
-      recheck_fc9_groups<RNG, INJ>(a, S, n, t, (int)(blockIdx.x * blockDim.x + threadIdx.x) >> 4,
-                                   groups);
-      if (decide) last_block_decides<KIND>(ctl);
-      return;
-    }
-  }
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    const int2 e = a.rlist[i];
-    const int c = e.x, k = e.y;
-    // The verdict needs one failing lane only, also for a candidate whose FP32
-    // rollout ran in full (the Newton iterate): its rechecks stop at the first
-    // FP64 violation too.
-    if (a.early &&
-        (__hip_atomic_load(&S->dead[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-         __hip_atomic_load(&S->fail64[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-      continue;
-    int jb = 0, ns = 0;
-    const int early = a.early;
-    const int q = S->q;
-    // chance-constrained verdict: one FP64 violation refuses the candidate only
-    // once more than q scenarios violate, so the lane does not stop on others'
-    const double m = rollout_lane<KIND, double, RNG, INJ>(
-        a, early, S->v[c], k, t, early && q == 0 ? &S->fail64[c] : nullptr, jb, ns, nullptr);
-    atomicMin(&S->key64[c], ord64(m));
-    if (q > 0) {
-      a.per_key[(size_t)c * a.N + k] = ord64(m);
-      if (m < 0.0 && S->nviol[c] + atomicAdd(&S->nviol64[c], 1) >= q)
-        __hip_atomic_store(&S->fail64[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else if (m < 0.0) {
-      __hip_atomic_store(&S->fail64[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
-  if (decide) last_block_decides<KIND>(ctl);
+  const GroupLane gl;
+  recheck_fc9_lanes<RNG, INJ>(a, S, S->n_recheck, a.st->t, gl,
+                              xch + gl.grp * kGroupStride<double>,
+                              (int)blockIdx.x * kWaveGroups + gl.grp,
+                              (int)gridDim.x * kWaveGroups);
+  if (decide) last_block_decides<2>(ctl);
 }
 
 // Batched serving: the FP64 recheck of every instance of a group in one launch,
@@ -1206,15 +910,15 @@ __global__ void __launch_bounds__(64) k_flat_recheck(const RollArgs<KIND, double
   const int n = S->n_recheck;
   const uint32_t t = a.st->t;
   if constexpr (KIND == 2) {
-    // few entries: the cooperative rollout, four groups of 16 lanes
-    if (n <= 8) {
-      recheck_fc9_groups<1, INJ>(a, S, n, t, (int)threadIdx.x >> 4, (int)blockDim.x >> 4);
-      __threadfence();
-      __syncthreads();
-      const CtlArgs<KIND>& cl = ctl[blockIdx.x];
-      decide_body<KIND>(cl.pc, cl.st, cl.srch, cl.grad);
-      return;
-    }
+    __shared__ __align__(16) double xch[kWaveSlots<double>];
+    const GroupLane gl;
+    recheck_fc9_lanes<1, INJ>(a, S, n, t, gl, xch + gl.grp * kGroupStride<double>, gl.grp,
+                              kWaveGroups);
+    __threadfence();
+    __syncthreads();
+    const CtlArgs<KIND>& cl = ctl[blockIdx.x];
+    decide_body<KIND>(cl.pc, cl.st, cl.srch, cl.grad);
+    return;
   }
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const int2 e = a.rlist[i];
@@ -3076,26 +2780,12 @@ hipError_t launch_rollout(const Problem& pr, double band, int precision, int ear
       });
     });
   }
-  if (cfg.lanes == 16 && precision == 0 && pr.p.kind == 2 && !cfg.chance && !(ckpt && cfg.tan)) {
-    // 9-state plant, one scenario per group of 16 lanes
-    const int gx = div_up((size_t)pr.s.N * 16, (size_t)cfg.block);
-    const dim3 grid(gx, cfg.cmax_round + gen_rows_for((size_t)gx * cfg.block));
-    auto a = make_args<2, float>(pr, band, early_exit, record, b);
-    a.ckpt = b.adj_ckpt;
-    a.Kc = Kc;
-    a.ckpt_cand = ckpt_cand;
-    set_gen(a);
-    return by_bit(pr.s.rng_mode, [&](auto rc) {
-      constexpr int R = decltype(rc)::value;
-      return by_bit(pr.s.inject, [&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        if (ckpt)
-          hipLaunchKernelGGL((k_rollout_fc9_group<R, I, 1>), grid, dim3(cfg.block), 0, st, a);
-        else
-          hipLaunchKernelGGL((k_rollout_fc9_group<R, I, 0>), grid, dim3(cfg.block), 0, st, a);
-        return hipGetLastError();
-      });
-    });
+  if (pr.p.kind == 2 &&
+      (precision == 1 || (cfg.lanes == 16 && !cfg.chance && !(ckpt && cfg.tan)))) {
+    const int gx = div_up((size_t)pr.s.N, (size_t)fc9_lanes_per_block(cfg.block));
+    return launch_rollout_fc9_lanes(pr, band, precision, early_exit, record, cfg, b, st,
+                                    ckpt ? ckpt_cand : -2, Kc,
+                                    gen_rows_for((size_t)gx * cfg.block), gen_w, gen_th);
   }
   if (precision == 1 && pr.p.kind == 1)  // 4-state plant in FP64: matrix cores
     return launch_rollout_lq4_mx(
@@ -3110,28 +2800,19 @@ hipError_t launch_rollout(const Problem& pr, double band, int precision, int ear
       constexpr int R = decltype(rc)::value;
       return by_bit(pr.s.inject, [&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        if (precision == 0) {
-          auto a = make_args<K, float>(pr, band, early_exit, record, b);
-          a.ckpt = b.adj_ckpt;
-          a.Kc = Kc;
-          a.ckpt_cand = ckpt_cand;
-          set_gen(a);
-          if (cfg.chance)  // no Newton search, hence no checkpoints
-            hipLaunchKernelGGL((k_rollout<K, float, R, I, 0, 1>), grid, dim3(cfg.block), 0, st, a);
-          else if (ckpt && cfg.tan)
-            hipLaunchKernelGGL((k_rollout<K, float, R, I, 2>), grid, dim3(cfg.block), 0, st, a);
-          else if (ckpt)
-            hipLaunchKernelGGL((k_rollout<K, float, R, I, 1>), grid, dim3(cfg.block), 0, st, a);
-          else
-            hipLaunchKernelGGL((k_rollout<K, float, R, I, 0>), grid, dim3(cfg.block), 0, st, a);
-        } else if constexpr (K == 2) {
-          auto a = make_args<K, double>(pr, 0.0, early_exit, record, b);
-          set_gen(a);
-          if (cfg.chance)
-            hipLaunchKernelGGL((k_rollout<K, double, R, I, 0, 1>), grid, dim3(cfg.block), 0, st, a);
-          else
-            hipLaunchKernelGGL((k_rollout<K, double, R, I, 0>), grid, dim3(cfg.block), 0, st, a);
-        }
+        auto a = make_args<K, float>(pr, band, early_exit, record, b);
+        a.ckpt = b.adj_ckpt;
+        a.Kc = Kc;
+        a.ckpt_cand = ckpt_cand;
+        set_gen(a);
+        if (cfg.chance)  // no Newton search, hence no checkpoints
+          hipLaunchKernelGGL((k_rollout<K, float, R, I, 0, 1>), grid, dim3(cfg.block), 0, st, a);
+        else if (ckpt && cfg.tan)
+          hipLaunchKernelGGL((k_rollout<K, float, R, I, 2>), grid, dim3(cfg.block), 0, st, a);
+        else if (ckpt)
+          hipLaunchKernelGGL((k_rollout<K, float, R, I, 1>), grid, dim3(cfg.block), 0, st, a);
+        else
+          hipLaunchKernelGGL((k_rollout<K, float, R, I, 0>), grid, dim3(cfg.block), 0, st, a);
         return hipGetLastError();
       });
     });
@@ -3158,15 +2839,15 @@ hipError_t launch_recheck(const Problem& pr, int early_exit, const LaunchCfg& cf
       });
     });
   }
-  // 9-state plant: up to one group of 16 lanes per possible entry (four per
-  // workgroup, at most 256 workgroups), for the cooperative FP64 rollout
-  const int blocks = (int)(div_up(cap, 4) < 256 ? div_up(cap, 4) : 256);
+  // 9-state plant: up to one group of 9 lanes per possible entry (seven per
+  // workgroup, at most 512 workgroups)
+  const int blocks = (int)(div_up(cap, kWaveGroups) < 512 ? div_up(cap, kWaveGroups) : 512);
   return by_bit(pr.s.rng_mode, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
     return by_bit(pr.s.inject, [&](auto ic) {
       constexpr int I = decltype(ic)::value;
       auto a = make_args<2, double>(pr, 0.0, early_exit, 0, b);
-      hipLaunchKernelGGL((k_recheck<2, R, I>), dim3(blocks), dim3(64), 0, st, a,
+      hipLaunchKernelGGL((k_recheck_fc9<R, I>), dim3(blocks), dim3(64), 0, st, a,
                          make_ctl<2>(pr, b, 0), decide);
       return hipGetLastError();
     });
