@@ -157,10 +157,11 @@ typedef struct rg_options {
     int32_t lanes;         /* lanes per scenario of FP32 rollouts: 1; 4 for LQ4 (one
                               scenario per quad, state split across lanes; robust or
                               chance-constrained verdict); 16 for FC9 (one scenario per group
-                              of 16 lanes, one lane per state component; robust verdict, not
+                              of lanes, one lane per state component; robust verdict, not
                               with the tangent-driven Newton search); 0 = auto (LQ4: 4; FC9:
-                              16 while a round holds at most 32768 scenario-candidate pairs,
-                              else 1).  kappa is the same in every layout; the 9-state
+                              16 while a round holds few scenario-candidate pairs (grid: at
+                              most 98304, else 32768), else 1).  FP64 rollouts have one
+                              layout each (LQ4: 4 lanes, FC9: groups), whatever this says.  kappa is the same in every layout; the 9-state
                               groups' margins are bit-identical to one lane's */
     int32_t Kc;            /* adjoint checkpoint interval in RK4 steps (default 50) */
     int32_t persistent_wgs;/* batches: workgroups of the persistent rollout kernel (0 = auto) */
@@ -170,6 +171,9 @@ typedef struct rg_options {
                               1); later rounds use the speculative tree.  Only which
                               candidates are evaluated early changes: the result is that of
                               sequential bisection either way.  0: tree from round 0.
+                              With depth = 0 and few scenarios the predicted round also
+                              evaluates the tree's first levels (a single step's also beside
+                              the probe alone), so that a wrong guess costs no round.
                               Newton searches: after a step that held v (kappa = 0), 1 makes
                               the first round test the kappa = 1 probe and the bisection path
                               2^-1 .. 2^-K towards 0, every candidate stopping at its first

@@ -24,6 +24,8 @@ struct rg_handle {
   Problem pr;
   rg_options opt;
   LaunchCfg cfg;
+  bool auto_depth = false;  // opt.depth was left to the library
+  int pred_tree = 0;        // tree levels of a predicted round 0
   // device memory
   hipStream_t stream = nullptr;
   void* ws = nullptr;
@@ -172,15 +174,21 @@ Layout layout_of(const rg_handle* h) {
   return L;
 }
 
-// Scenario-candidate pairs of one round up to which the 9-state FP32 rollouts
-// run one scenario per group of 16 lanes (auto lanes): one lane per scenario
-// leaves the chip mostly idle there and each round is bound by the latency of
-// a whole RK4 step on one lane; with more pairs the groups' extra instructions
-// (exchanges, lanes 9..15) cost more than the latency they save (measured:
-// the 32-point grid at H = 1024 is 2.7x faster with groups at 16384 pairs,
-// 2.0x at 32768, slower from about 100000; the adjoint Newton search 1.7x
-// faster at N = 4096 and 10 % slower at N = 16384).
-constexpr double kGroupPairsMax = 32768;
+// 9-state FP32 rollouts, auto lanes: up to these scenario-candidate pairs of a
+// round they run one scenario per group of lanes: one lane per scenario leaves
+// the chip mostly idle there, and each round is bound by the latency of a whole
+// RK4 step on one lane; with more pairs the groups' exchanges cost more than
+// the latency they save.  Grid (rows die early): the 32-point grid at N = 2048
+// H = 700 takes 1.11 ms with groups and 1.63 with one lane, 1.46 and 1.53 at
+// N = 4096.  Bisection, in rounds of depth 2: N = 4096 H = 700 4.4 and 5.4 ms
+// per update, N = 8192 5.3 and 6.4, N = 16384 8.1 and 7.9.  Newton: rounds of
+// four candidates, one of them over the full horizon.
+constexpr double kGroupPairsGrid = 98304, kGroupPairs = 32768;
+bool groups_pay(const rg_handle* h) {
+  const double N = h->pr.s.N;
+  if (h->opt.search == RG_SEARCH_GRID) return h->opt.M * N <= kGroupPairsGrid;
+  return (is_newton(h->opt.search) ? 4 : 3) * N <= kGroupPairs;
+}
 
 int lanes_for(const rg_handle* h) {
   const bool f32_robust = h->opt.precision == RG_PREC_F32_RECHECK && h->opt.chance_q == 0;
@@ -192,51 +200,65 @@ int lanes_for(const rg_handle* h) {
   if (h->opt.lanes == 4) return quad_ok ? 4 : 1;
   if (h->opt.lanes == 16) return group_ok ? 16 : 1;
   if (h->opt.lanes == 1) return 1;
-  return quad_ok ? 4 : (group_ok ? 16 : 1);
+  return quad_ok ? 4 : (group_ok && groups_pay(h) ? 16 : 1);
+}
+
+// Waves one candidate of a round occupies, and the waves per round up to which
+// more candidates cost little: a round is then bound by one wave's chain of
+// steps, and beyond it they cost their full time.  Two per SIMD for the 4-state
+// plant (quads and matrix layout alike) and the 9-state FP64 groups, 4.5 for the
+// 9-state FP32 groups, one for the 9-state one-lane rollouts (which keep the
+// vector ALU busy at one).  Per update, FP64 4-state: N = 1024 H = 1000 depth
+// 3 / 4 / 5: 0.61 / 0.52 / 0.58 ms, N = 4096 H = 2000 depth 2 / 3 / 4: 1.57 /
+// 1.48 / 1.65; 9-state H = 700, groups: N = 2048 depth 3 / 4 3.7 / 3.4 ms, N =
+// 8192 depth 2 / 3 5.3 / 5.6; FP64: N = 512 depth 3 / 4 / 5 3.8 / 3.3 / 3.4 ms;
+// one lane: N = 16384 depth 2 / 3 / 4 7.9 / 8.2 / 8.6.
+double waves_per_candidate(const rg_handle* h, int lanes) {
+  const double N = h->pr.s.N;
+  if (h->pr.p.kind == RG_PLANT_FC9)  // groups: seven scenarios per wave
+    return lanes == 16 || h->opt.precision == RG_PREC_F64 ? N / 7.0 : N / 64.0;
+  return lanes == 4 || h->opt.precision == RG_PREC_F64 ? N / 16.0 : N / 64.0;
+}
+double wave_budget(const rg_handle* h, int lanes) {
+  double per_simd = 2.0;
+  if (h->pr.p.kind == RG_PLANT_FC9 && h->opt.precision != RG_PREC_F64)
+    per_simd = lanes == 16 ? 4.5 : 1.0;
+  return per_simd * 256 * 4;
 }
 
 int depth_for(const rg_handle* h, int lanes) {
-  if (h->opt.depth > 0) return h->opt.depth;
-  // As many levels as keep a round's waves within the budget: up to it more
-  // candidates cost little (a round is bound by one wave's chain of steps),
-  // beyond it they cost their full time, while each level halves the bracket
-  // only once.  Then the smallest depth that needs no more rounds.
-  // 4-state plant: two waves per SIMD (4 lanes per scenario, FP32 quads and FP64
-  // matrix layout alike).  Per update, FP64: N = 1024 H = 1000 depth 3 / 4 / 5:
-  // 0.61 / 0.52 / 0.58 ms; N = 4096 H = 2000 depth 2 / 3 / 4: 1.57 / 1.48 /
-  // 1.65 ms.  Two levels at least: N = 16384 H = 1000 depth 1 / 2 / 3: 1.71 /
-  // 1.65 / 1.92 ms (half of the extra candidates die early).
-  // 9-state plant: four.
-  const bool lq4 = h->pr.p.kind == RG_PLANT_LQ4;
+  if (h->opt.depth > 0) return h->opt.depth;  // the caller's, or already resolved
+  // As many levels as keep a round's waves within the budget, two at least (half
+  // of the extra candidates die early: 4-state N = 16384 H = 1000 depth 1 / 2 /
+  // 3: 1.71 / 1.65 / 1.92 ms), then the smallest depth that needs no more rounds.
   const int goal = h->opt.search == RG_SEARCH_GRID ? h->opt.refine : h->opt.K;
-  const double lanes_budget = (lq4 ? 2.0 : 4.0) * 256 * 4 * 64;
-  if (lq4 && h->opt.precision == RG_PREC_F64) lanes = 4;
-  const double per_cand = (double)h->pr.s.N * lanes;
-  int dmax = lq4 ? 2 : 1;
-  while (dmax < 6 && ((1 << (dmax + 1)) - 1) * per_cand <= lanes_budget) ++dmax;
+  const double per_cand = waves_per_candidate(h, lanes), budget = wave_budget(h, lanes);
+  int dmax = 2;
+  while (dmax < 6 && ((1 << (dmax + 1)) - 1) * per_cand <= budget) ++dmax;
   if (goal <= 0) return 1;
   const int rounds = (goal + dmax - 1) / dmax;
   return (goal + rounds - 1) / rounds;
 }
 
-void plan_with(rg_handle* h, int lanes);
-
-void plan(rg_handle* h) {
-  const bool auto_lanes = h->opt.lanes == 0;
-  const int depth0 = h->opt.depth;  // 0: auto
-  plan_with(h, lanes_for(h));
-  // auto: 9-state groups only for rounds of few scenario-candidate pairs
-  if (auto_lanes && h->cfg.lanes == 16 &&
-      (double)h->cfg.cmax_round * h->pr.s.N > kGroupPairsMax) {
-    h->opt.depth = depth0;
-    plan_with(h, 1);
-  }
+// Levels of the bisection tree that a predicted round 0 also evaluates, so that
+// a wrong guess costs no round: as many as keep the whole round (probe, tree,
+// the predicted path below it) within the wave budget; none with a depth the
+// caller chose.
+int pred_tree_for(const rg_handle* h, int lanes) {
+  const int K = h->opt.K;
+  if (!h->auto_depth || h->opt.search != RG_SEARCH_BISECT || !h->opt.predict) return 0;
+  const double per_cand = waves_per_candidate(h, lanes), budget = wave_budget(h, lanes);
+  int d = 0;
+  while (d < 6 && d < K && (1 + ((1 << (d + 1)) - 1) + K - (d + 1)) * per_cand <= budget) ++d;
+  return d > 1 ? d : 0;  // the path holds the tree's first level anyway
 }
 
-void plan_with(rg_handle* h, int lanes) {
+void plan(rg_handle* h) {
+  const int lanes = lanes_for(h);
   const int d = depth_for(h, lanes);
   h->opt.depth = d;
   h->opt.lanes = lanes;
+  h->pred_tree = pred_tree_for(h, lanes);
   LaunchCfg c;
   c.lanes = lanes;
   c.block = h->opt.block > 0 ? h->opt.block : 256;
@@ -257,7 +279,8 @@ void plan_with(rg_handle* h, int lanes) {
     c.cmax_round = r0 > tree ? r0 : tree;
     c.rounds = 1 + (h->opt.K - d0 + d - 1) / d;
     if (h->opt.predict) {  // round 0: probe + the predicted path (K midpoints), or the probe alone
-      if (1 + h->opt.K > c.cmax_round) c.cmax_round = 1 + h->opt.K;
+      const int t = h->pred_tree, pred = 1 + ((1 << t) - 1) + h->opt.K - t;
+      if (pred > c.cmax_round) c.cmax_round = pred;
       c.rounds = 1 + (h->opt.K + d - 1) / d;
     }
   }
@@ -282,6 +305,7 @@ void fill_search(const rg_handle* h, DevSearch* S, int32_t spec_depth, int32_t s
   S->pred = std::nan("");
   S->K = h->opt.K;
   S->depth = h->opt.depth;
+  S->pred_tree = h->pred_tree;
   S->M = h->opt.M;
   S->refine = h->opt.refine;
   S->precision = h->opt.precision;
@@ -782,6 +806,7 @@ int rg_create(const rg_plant* plant, const rg_scenarios* scen, const rg_constrai
   h->pr.H = H;
   h->pr.dt = dt;
   h->opt = o;
+  h->auto_depth = o.depth == 0;
   plan(h);
   *out = h;
   return RG_OK;
@@ -1218,12 +1243,17 @@ int reset_search_schedule(rg_handle* h) {
                              sizeof(predict), hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, hipMemcpyAsync((char*)h->b.srch + offsetof(DevSearch, pred), &none, sizeof(none),
                              hipMemcpyHostToDevice, h->stream));
+    const int32_t pred_tree = h->pred_tree;
+    HIPCHK(h, hipMemcpyAsync((char*)h->b.srch + offsetof(DevSearch, pred_tree), &pred_tree,
+                             sizeof(pred_tree), hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
   }
   return RG_OK;
 }
 
-int apply_schedule(rg_handle* h, const rg_options& o) {
+// auto_depth: o.depth is the library's own choice, not a schedule's.
+int apply_schedule(rg_handle* h, const rg_options& o, bool auto_depth) {
+  h->auto_depth = auto_depth;
   h->opt.lanes = o.lanes;
   h->opt.block = o.block;
   h->opt.depth = o.depth;
@@ -1248,6 +1278,7 @@ int rg_autotune(rg_handle* h, const double* x0, double v0, const double* r_seq, 
   int rc = ensure_workspace(h);
   if (rc) return rc;
   const rg_options own = h->opt;
+  const bool own_auto = h->auto_depth;
   const uint32_t t0 = h->t;
   const bool f32_robust = h->opt.precision == RG_PREC_F32_RECHECK && h->opt.chance_q == 0;
   const bool quad_ok = h->pr.p.kind == RG_PLANT_LQ4 && f32_robust;
@@ -1282,7 +1313,7 @@ int rg_autotune(rg_handle* h, const double* x0, double v0, const double* r_seq, 
   double best_ms = INFINITY;
   rg_options best = own;
   for (const rg_options& o : cands) {
-    if ((rc = apply_schedule(h, o))) break;
+    if ((rc = apply_schedule(h, o, false))) break;
     // the first run captures the graphs; the faster of the next two counts
     double ms = INFINITY;
     for (int rep = 0; rep < 3 && rc == RG_OK; ++rep) {
@@ -1309,7 +1340,8 @@ int rg_autotune(rg_handle* h, const double* x0, double v0, const double* r_seq, 
   }
   h->t = t0;
   h->gen_t = -1;  // the streamed draws no longer match the step counter
-  const int rc2 = apply_schedule(h, (rc == RG_OK && apply) ? best : own);
+  const bool keep = rc == RG_OK && apply;
+  const int rc2 = apply_schedule(h, keep ? best : own, !keep && own_auto);
   if (rc) return rc;
   if (rc2) return rc2;
   if (best_out) *best_out = best;

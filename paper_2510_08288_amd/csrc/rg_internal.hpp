@@ -78,6 +78,7 @@ struct DevSearch {
   // Bisection: round 0 speculates along the path to the previous step's kappa
   int32_t predict;                    // 1: enabled
   double pred;                        // previous step's kappa (NaN: none yet)
+  int32_t pred_tree;                  // levels of the tree that round 0 also evaluates (0: none)
   // Workgroups of the current recheck launch that have finished; the last one
   // takes the round's decision and resets the count.
   uint32_t blocks_done;

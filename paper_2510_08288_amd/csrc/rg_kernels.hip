@@ -1373,16 +1373,24 @@ __device__ void setup_body(const typename Plant<KIND, double>::Coef& pc, DevStat
             S->spec_n = d;
             S->spec_used = 0;
             S->n_cand = 1 + d;
+          } else if (!closed_loop) {  // single steps: the tree beside the probe
+            s_tree = S->pred_tree;
+            S->n_cand = 1 << s_tree;
           }
         } else {
+          // the tree's levels, then the path below them
+          const int K = S->K;
+          const bool hold = pa && closed_loop && pr == 0.0 && S->spec_hold > 0;
+          const int tr = hold ? 0 : S->pred_tree, nn = (1 << tr) - 1;
+          s_tree = tr;
           double lo = 0.0, hi = 1.0;
-          for (int l = 0; l < S->K; ++l) {
+          for (int l = 0; l < K; ++l) {
             const double m = midpoint(lo, hi);
-            S->kappa[1 + l] = m;
+            if (l >= tr) S->kappa[1 + nn + l - tr] = m;
             if (pr >= m) lo = m;
             else hi = m;
           }
-          S->n_cand = 1 + S->K;
+          S->n_cand = 1 + nn + K - tr;
           // The governor held v (kappa = 0): the round also runs the first
           // rounds of the next steps (probe and midpoints towards 0), from the
           // states they start in if they hold v too (the same FP64 true-plant
@@ -2085,7 +2093,7 @@ struct AdjArgs {
 
 template <int KIND, int RNG, int INJ>
 __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, const AdjArgs g) {
-  using P = Plant<KIND, float>;
+  using P = AdjPlant<KIND>;
   constexpr int n = P::n;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= g.grad->n_entries) return;
@@ -2125,7 +2133,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
   auto step = [&](float* x, const float* w) {
     float s[n];
     forcing(w, s);
-    rk4_step<KIND, float>(a.pc, Ln, s, a.h, a.hh, a.h6, x);
+    rk4_step<KIND, float, P>(a.pc, Ln, s, a.h, a.hh, a.h6, x);
     if (INJ == 1) P::post(a.pc, w, x);
   };
   // forward: minimiser and checkpoints
@@ -2176,7 +2184,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
         load_w(j, w);
         float s[n];
         forcing(w, s);
-        rk4_vjp<KIND, float>(a.pc, Ln, s, a.h, a.hh, a.h6, xs, lam, vb, tb);
+        rk4_vjp<KIND, float, P>(a.pc, Ln, s, a.h, a.hh, a.h6, xs, lam, vb, tb);
       }
     }
   } else {
