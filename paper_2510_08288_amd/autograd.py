@@ -37,9 +37,9 @@ class ScenarioMargins(torch.autograd.Function):
         gov = ctx.gov
         gov.set_step(ctx.t)
         up = grad_m.detach().cpu().numpy().astype(np.float32)
-        g = gov.grad(ctx.x, ctx.r, ctx.v_prev, ctx.kappa, upstream=up)
-        dk = torch.tensor(g["dkappa"], dtype=torch.float64)
-        dth = torch.from_numpy(g["dtheta"].copy()) if ctx.has_theta else None
+        dkappa, dtheta = gov._weighted_grad(ctx.x, ctx.r, ctx.v_prev, ctx.kappa, up)
+        dk = torch.tensor(dkappa, dtype=torch.float64)
+        dth = torch.from_numpy(dtheta.copy()) if ctx.has_theta else None
         return dk, dth, None, None, None, None
 
 

@@ -1109,9 +1109,12 @@ int rg_grad(rg_handle* h, const double* x, double r, double v_prev, double kappa
                            hipMemcpyHostToDevice, h->stream));
   HIPCHK(h, launch_setup_list(h->pr, h->b, 1, h->stream));
   // arg-min scenario from the FP32 rollouts (keys carry the scenario index)
-  HIPCHK(h, launch_rollout(h->pr, h->opt.band, RG_PREC_F32_RECHECK, 0, 1, cfg, h->b, h->stream,
-                           upstream ? -2 : 0, h->opt.Kc));
-  HIPCHK(h, launch_recheck(h->pr, 0, cfg, h->b, h->stream));
+  // and the margin; a weighted sum without the margin needs neither
+  if (!upstream || margin_out) {
+    HIPCHK(h, launch_rollout(h->pr, h->opt.band, RG_PREC_F32_RECHECK, 0, 1, cfg, h->b, h->stream,
+                             upstream ? -2 : 0, h->opt.Kc));
+    HIPCHK(h, launch_recheck(h->pr, 0, cfg, h->b, h->stream));
+  }
   int max_entries = 1;
   if (upstream) {
     const int32_t cnt = (int32_t)ks.size();

@@ -591,60 +591,15 @@ struct Plant<2, T> {
   }
 };
 
-// The plant as the weighted adjoint runs it.  The derivative of a scenario's
-// margin is that at its first minimising step, and which step that is hangs, at
-// a flat minimum, on the last bits of the trajectory; so the 9-state sweeps keep
-// one arithmetic of their own (tanh itself in the coupling sum, the constant
-// terms of phi_7 and phi_9 per evaluation), whatever the rollouts' becomes.
-template <int KIND>
-struct AdjPlant : Plant<KIND, float> {};
-template <>
-struct AdjPlant<2> : Plant<2, float> {
-  using P = Plant<2, float>;
-  __device__ static void lane_init(const Coef& c, const float* th, float v, Lane& L) {
-    P::lane_init(c, th, v, L);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) L.axb[i] = __fmul_rn(L.a[i], c.xbar[i]);
-  }
-  __device__ static void deriv(const Coef& c, const Lane& L, const float* s, const float* x,
-                               float* xd) {
-#pragma clang fp contract(off)
-    float tz[9], r[6];
-#pragma unroll
-    for (int j = 0; j < 9; ++j) tz[j] = t_tanh_shift(x[j], c.nkxbar[j]);
-#pragma unroll
-    for (int l = 0; l < 6; ++l) r[l] = orifice(x[l], (l < 5) ? x[l + 1] : c.p_amb);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      float a = s[i];
-      if (i < 6) a = t_fma(-L.kq[i < 6 ? i : 0], r[i < 6 ? i : 0], a);
-      else if (i != 7) a = t_fma(L.b[i - 6], L.v, a);
-      a = t_fma(-L.a[i], x[i], a);
-#pragma unroll
-      for (int j = 0; j < 9; ++j) a = t_fma(L.W[9 * i + j], tz[j], a);
-      if (i == 0) a = t_fma(c.c_q0, x[6], a);
-      else if (i < 6) a = t_fma(L.kq[i - 1], r[i - 1], a);
-      else if (i == 6) a = t_fma(-(L.mu[0] * x[6]), x[0] - c.p1ref, a);
-      else if (i == 7) a = t_fma(L.b2v, x[6], a);
-      else a = t_fma(-(L.mu[1] * (x[8] - 1.0f)), L.v, a);
-      xd[i] = a;
-    }
-  }
-  __device__ static void output(const Coef& c, const Lane&, const float* x, float* y) {
-    y[0] = c.c_q0 * x[6] / t_fma(c.d1, x[8], c.d0);
-    y[1] = x[0];
-    y[2] = x[6];
-  }
-};
-
 // ---------------------------------------------------------------------------
 // Classical RK4 step with the step forcing s held: the stage increments are
 // accumulated as k1 + 2 k2 + 2 k3 + k4.
 // ---------------------------------------------------------------------------
-template <int KIND, class T, class P = Plant<KIND, T>>
+template <int KIND, class T>
 __device__ __forceinline__ void rk4_step(const typename Plant<KIND, T>::Coef& c,
                                          const typename Plant<KIND, T>::Lane& L, const T* s,
                                          T h, T hh, T h6, T* x) {
+  using P = Plant<KIND, T>;
   T k[P::n], acc[P::n], xs[P::n];
   P::deriv(c, L, s, x, k);
 #pragma unroll
@@ -717,11 +672,12 @@ __device__ __forceinline__ void rk4_step_tan(const typename Plant<KIND, T>::Coef
 
 // Reverse sweep of one RK4 step at x with forcing s: lam <- (dPhi/dx)^T lam,
 // vb += lam . dPhi/dv, tb += lam . dPhi/dtheta.  Stage states are recomputed.
-template <int KIND, class T, class P = Plant<KIND, T>>
+template <int KIND, class T>
 __device__ __forceinline__ void rk4_vjp(const typename Plant<KIND, T>::Coef& c,
                                         const typename Plant<KIND, T>::Lane& L, const T* s,
                                         T h, T hh, T h6, const T* x, T* lam, double& vb,
                                         double* tb) {
+  using P = Plant<KIND, T>;
   constexpr int n = P::n;
   T x2[n], x3[n], x4[n], k[n];
   P::deriv(c, L, s, x, k);

@@ -16,6 +16,7 @@
 // No step reads back to the host.  All search state lives in DevSearch.
 #include <hip/hip_runtime.h>
 
+#include "rg_adjoint.hpp"
 #include "rg_fc9_lanes.hpp"
 #include "rg_lq4_mx.hpp"
 
@@ -2077,23 +2078,9 @@ __global__ void k_traj(const RollArgs<KIND, T> a, T v, const int32_t* k_list, in
 // in reverse with rk4_vjp.  States and adjoints in FP32, parameter sums in
 // FP64.  One lane per (scenario, upstream weight) entry.
 // ---------------------------------------------------------------------------
-struct AdjArgs {
-  int Kc;
-  int lmax;                // stride of the SoA scratch (= N)
-  int cand;                // candidate index whose v is used
-  const int32_t* k_list;
-  const float* w_list;
-  float* out_m;
-  double* out_dv;
-  double* out_dth;
-  float* ckpt;
-  float* seg;
-  DevGrad* grad;
-};
-
 template <int KIND, int RNG, int INJ>
 __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, const AdjArgs g) {
-  using P = AdjPlant<KIND>;
+  using P = Plant<KIND, float>;
   constexpr int n = P::n;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= g.grad->n_entries) return;
@@ -2133,7 +2120,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
   auto step = [&](float* x, const float* w) {
     float s[n];
     forcing(w, s);
-    rk4_step<KIND, float, P>(a.pc, Ln, s, a.h, a.hh, a.h6, x);
+    rk4_step<KIND, float>(a.pc, Ln, s, a.h, a.hh, a.h6, x);
     if (INJ == 1) P::post(a.pc, w, x);
   };
   // forward: minimiser and checkpoints
@@ -2184,7 +2171,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
         load_w(j, w);
         float s[n];
         forcing(w, s);
-        rk4_vjp<KIND, float, P>(a.pc, Ln, s, a.h, a.hh, a.h6, xs, lam, vb, tb);
+        rk4_vjp<KIND, float>(a.pc, Ln, s, a.h, a.hh, a.h6, xs, lam, vb, tb);
       }
     }
   } else {
@@ -2547,32 +2534,32 @@ __global__ void k_grad_prepare(const CtlArgs<KIND> a, DevGrad* G, int32_t* adj_k
 }
 
 // Deterministic sum of the entries' weighted derivatives (fixed order per
-// thread, then a fixed LDS tree), then dM/dkappa = dM/dv (r - v_prev).
+// thread, then a fixed LDS tree), one workgroup per component: workgroup 0 the
+// set-point, then dM/dkappa = dM/dv (r - v_prev).  (One workgroup taking the 21
+// components in turn needed 48 us.)
 __global__ void __launch_bounds__(256) k_grad_reduce(DevGrad* G, const double* dv, const double* dth,
-                                                     int nth, const DevState* st,
-                                                     const DevSearch* S, int cand) {
+                                                     const DevState* st, const DevSearch* S,
+                                                     int cand) {
   if (cand < 0 && (S->done || S->nk_idx < 0)) return;  // finished, or no iterate this round
   __shared__ double sh[256];
   const int n = G->n_entries;
-  const int tid = threadIdx.x;
-  for (int c = -1; c < nth; ++c) {
-    double acc = 0.0;
-    for (int e = tid; e < n; e += 256) acc += c < 0 ? dv[e] : dth[(size_t)e * kMaxTh + c];
-    sh[tid] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (tid < s) sh[tid] += sh[tid + s];
-      __syncthreads();
-    }
-    if (tid == 0 && n > 0) {
-      if (c < 0) G->dM_dv += sh[0];
-      else G->dM_dth[c] += sh[0];
-    }
+  const int tid = threadIdx.x, c = (int)blockIdx.x - 1;
+  double acc = 0.0;
+  for (int e = tid; e < n; e += 256) acc += c < 0 ? dv[e] : dth[(size_t)e * kMaxTh + c];
+  sh[tid] = acc;
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (tid < s) sh[tid] += sh[tid + s];
     __syncthreads();
   }
-  if (tid == 0) {  // v = r exactly at kappa = 1; dv/dkappa = r - v_prev on both sides
-    G->dM_dkappa = G->dM_dv * (st->r - st->v_prev);
+  if (tid != 0) return;
+  if (c >= 0) {
+    if (n > 0) G->dM_dth[c] += sh[0];
+    return;
   }
+  if (n > 0) G->dM_dv += sh[0];
+  // v = r exactly at kappa = 1; dv/dkappa = r - v_prev on both sides
+  G->dM_dkappa = G->dM_dv * (st->r - st->v_prev);
 }
 
 
@@ -2931,17 +2918,14 @@ hipError_t launch_adjoint(const Problem& pr, int Kc, int max_entries, const DevB
   g.ckpt = b.adj_ckpt;
   g.seg = b.adj_seg;
   g.grad = b.grad;
-  return by_kind(pr.p.kind, [&](auto kc) {
-    constexpr int K = decltype(kc)::value;
-    return by_bit(pr.s.rng_mode, [&](auto rc) {
-      constexpr int R = decltype(rc)::value;
-      return by_bit(pr.s.inject, [&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        auto a = make_args<K, float>(pr, 0.0, 0, 0, b);
-        hipLaunchKernelGGL((k_adjoint<K, R, I>), dim3(div_up(max_entries, 64)), dim3(64), 0, st, a,
-                           g);
-        return hipGetLastError();
-      });
+  if (pr.p.kind == 2) return launch_adjoint_fc9(pr, g, max_entries, b, st);
+  return by_bit(pr.s.rng_mode, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    return by_bit(pr.s.inject, [&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      auto a = make_args<1, float>(pr, 0.0, 0, 0, b);
+      hipLaunchKernelGGL((k_adjoint<1, R, I>), dim3(div_up(max_entries, 64)), dim3(64), 0, st, a, g);
+      return hipGetLastError();
     });
   });
 }
@@ -2995,7 +2979,7 @@ hipError_t launch_tan_grad(const Problem& pr, const DevBuffers& b, int cand, hip
 hipError_t launch_grad_reduce(const DevBuffers& b, int max_entries, int nth, int cand,
                               hipStream_t st) {
   (void)max_entries;
-  hipLaunchKernelGGL(k_grad_reduce, dim3(1), dim3(256), 0, st, b.grad, b.adj_dv, b.adj_dth, nth,
+  hipLaunchKernelGGL(k_grad_reduce, dim3(1 + nth), dim3(256), 0, st, b.grad, b.adj_dv, b.adj_dth,
                      b.st, b.srch, cand);
   return hipGetLastError();
 }

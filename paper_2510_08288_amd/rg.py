@@ -341,6 +341,17 @@ class Governor:
                                    _ptr(dth)))
         return dict(M=M.value, dkappa=dk.value, dtheta=dth[: self.problem.n_theta])
 
+    def _weighted_grad(self, x, r: float, v_prev: float, kappa: float, upstream):
+        """The weighted sum of grad() without M(kappa), whose rollouts it then does not need."""
+        x = _f64(x)
+        up = np.ascontiguousarray(np.asarray(upstream, dtype=np.float32).reshape(-1))
+        assert up.size == self.problem.N
+        dk = C.c_double()
+        dth = np.zeros(max(self.problem.n_theta, 1))
+        self._check(self.L.rg_grad(self.h, _ptr(x), float(r), float(v_prev), float(kappa),
+                                   _ptr(up, _fp), None, C.byref(dk), _ptr(dth)))
+        return dk.value, dth[: self.problem.n_theta]
+
     def tangent(self, x, r: float, v_prev: float, kappa: float) -> dict:
         """rg_tangent: per-scenario FP32 margins, their forward-mode dm/dv and
         minimising steps, M(kappa) and dM/dkappa."""
