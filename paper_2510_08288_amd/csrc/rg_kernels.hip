@@ -2747,6 +2747,10 @@ hipError_t launch_rollout(const Problem& pr, double band, int precision, int ear
   };
   if (cfg.lanes == 4 && precision == 0 && pr.p.kind == 1 && quad_draws_addressable(pr) &&
       !(cfg.chance && (record || ckpt))) {
+    if (record && !early_exit && !ckpt && !gen) {  // a set-point sweep
+      const int cpl = sweep_candidates_per_lane(pr, cfg.cmax_round);
+      if (cpl > 0) return launch_sweep_lq4(pr, band, cfg.cmax_round, cpl, b, st);
+    }
     const int gx = div_up((size_t)pr.s.N * 4, (size_t)cfg.block);
     const dim3 grid(gx, cfg.cmax_round + gen_rows_for((size_t)gx * cfg.block));
     const QuadCoef qc = make_quad_coef(pr);

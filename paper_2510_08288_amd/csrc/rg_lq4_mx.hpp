@@ -68,6 +68,14 @@ __device__ __forceinline__ double mx_min(double v) {
   return v;
 }
 
+// A wave-uniform pointer in scalar registers.
+__device__ __forceinline__ const char* uniform_ptr(const void* ptr) {
+  const uint64_t p = (uint64_t)ptr;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32));
+  return (const char*)(((uint64_t)hi << 32) | lo);
+}
+
 // One lane's share of the model.  RNG 0 (streamed draws): one value per lane
 // holds the two disturbances of two steps, component l >> 4 being w0, w1 of the
 // even step and w0, w1 of the odd one, and E selects a step's pair.  RNG 1: the
@@ -149,22 +157,19 @@ __device__ __forceinline__ int mx_rollout(const MxLane<RNG, INJ>& M, const RollA
   // the horizon reads as zero.
   const uint32_t row = 8u * (uint32_t)a.N;
   const uint32_t off = 4u * (uint32_t)k + (q & 1) * 4u * (uint32_t)a.N + (q >> 1) * row;
-  const char* wsrc = RNG == 0 ? (const char*)step_w(a, t) : nullptr;
-  if constexpr (RNG == 0) {  // uniform: in scalar registers
-    const uint64_t p = (uint64_t)wsrc;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-    wsrc = (const char*)(((uint64_t)hi << 32) | lo);
-  }
+  const char* wsrc = RNG == 0 ? uniform_ptr(step_w(a, t)) : nullptr;
   auto load = [&](int j, float* w) {
     if constexpr (RNG == 0) {
       const int rows = H - j < U ? (H - j > 0 ? H - j : 0) : U;
       const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(
           (void*)(wsrc + (uint64_t)j * row), (short)0, (int)(row * (uint32_t)rows), 0x00020000);
+      // The range check compares the lane's offset with the record count minus
+      // the scalar offset, unsigned: the scalar offset must not exceed the count.
 #pragma unroll
       for (int u = 0; u < U / 2; ++u)
         w[u] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(res, off, 2u * (uint32_t)u * row, 0));
+            float, __builtin_amdgcn_raw_buffer_load_b32(
+                       res, off, row * (uint32_t)(2 * u < rows ? 2 * u : rows), 0));
     } else {
 #pragma unroll
       for (int u = 0; u < U / 4; ++u) {
@@ -216,5 +221,12 @@ __device__ __forceinline__ int mx_rollout(const MxLane<RNG, INJ>& M, const RollA
 hipError_t launch_rollout_lq4_mx(const Problem& pr, double band, int early_exit, int record,
                                  const LaunchCfg& cfg, const DevBuffers& b, hipStream_t st,
                                  int gen_rows, float* gen_w, float* gen_th);
+
+// FP32 set-point sweeps (full horizon, per-scenario margins recorded): how many
+// candidates per lane the one-lane matrix layout takes for M candidates, 0 where
+// the quad layout is faster.
+int sweep_candidates_per_lane(const Problem& pr, int M);
+hipError_t launch_sweep_lq4(const Problem& pr, double band, int M, int cpl, const DevBuffers& b,
+                            hipStream_t st);
 
 }  // namespace rg
