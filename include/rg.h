@@ -429,11 +429,14 @@ int rg_equilibrium(rg_handle* h, double v, double* x_out);
 /* A batch of `count` independent governors (own plant, scenarios, constraints,
  * H and dt each; the paper notes one small governor gains little from a GPU,
  * Sec. IV-B).  Each instance keeps its own search record and FP64 recheck list
- * in one device allocation, and its draws are regenerated inside the kernels
- * (the scenarios' rng_mode is ignored).  One search round of the whole batch is
- * one flat rollout launch per group of instances with the same plant kind and
- * injection (all their scenario tiles in one grid, FP32, one lane per
- * scenario), then each instance's FP64 recheck and decision.  All instances
+ * in one device allocation; the draws of all instances (4 B x N x H x n_w
+ * each) are generated once per step into a second one where they fit in 16 GiB
+ * and a quarter of the free memory, and regenerated inside the kernels otherwise
+ * (the scenarios' rng_mode is ignored; results are the same).  One search round
+ * of the instances with the same plant kind, injection and rollout layout is one
+ * flat rollout launch (all their scenario tiles in one grid, FP32, one lane per
+ * scenario, or for the longest horizons of the 9-state plant a group of lanes),
+ * then their FP64 rechecks and decisions.  All instances
  * use one search depth (opt.depth = 0: from the sum of N over the batch; large
  * batches evaluate one candidate per round).  opt: precision F32_RECHECK,
  * search BISECT or GRID, chance_q 0 (else RG_E_NOTSUP); block is the scenario

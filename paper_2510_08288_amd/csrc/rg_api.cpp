@@ -1439,17 +1439,21 @@ int rg_trajectory(rg_handle* h, const double* x, double v, const int32_t* k_list
 // ---------------------------------------------------------------------------
 // Many independent governors stepped together.  Each instance keeps its own
 // search record, result record and recheck list, carved from one device
-// allocation, and its draws are regenerated inside the kernels (a batch of a
-// thousand instances could not hold draw buffers).  One search round of the
-// whole batch is one flat rollout launch per group of instances with the same
-// plant kind and disturbance injection (every instance's scenario tiles side by
-// side in one grid, each workgroup reading its instance's argument block from
-// device memory), then one flat launch per group for the FP64 recheck and the
-// round's decision (one workgroup per instance).  A batched step starts with
-// the instances' round-0 setup and ends with their result records (one launch
-// per group each); it is captured once as a HIP graph and replayed.
+// allocation.  Its draws are generated once per step into a second allocation
+// where all of them fit in kBatchDrawBytes, else regenerated inside the kernels
+// (a batch of a thousand instances could not hold draw buffers).  One search
+// round of a group of instances (same plant kind, disturbance injection and
+// rollout layout) is one flat rollout launch (every instance's scenario tiles
+// side by side in one grid, each workgroup reading its instance's argument block
+// from device memory), then one flat launch for the FP64 recheck and the round's
+// decision.  A group's step starts with its instances' round-0 setup and ends
+// with their result records.  The groups share nothing, so each runs its whole
+// step on a stream of its own, forked from and joined to the batch's stream; the
+// step is captured once as a HIP graph and replayed.
+constexpr double kBatchDrawBytes = 16.0 * (1 << 30);
+constexpr int kBatchSide = 3;  // streams beside the batch's own
 struct BatchGroup {
-  int kind = 0, inject = 0, tiles = 0, cmax = 0;
+  int kind = 0, inject = 0, lanes = 1, tiles = 0, cmax = 0, rounds = 0;
   std::vector<int> members;     // batch indices of the group's instances
   void* args = nullptr;         // device: the members' FP32 rollout argument blocks
   void* args64 = nullptr;       // device: their FP64 recheck argument blocks
@@ -1467,10 +1471,12 @@ struct rg_batch {
   std::vector<uint32_t> t;       // per-instance RG step counters
   std::vector<BatchGroup> groups;
   int tile = 256;                // scenarios per rollout workgroup
-  int rounds = 0;                // device rounds per batched step (the largest plan)
   hipStream_t stream = nullptr;  // the caller's stream (NULL: own_stream)
   hipStream_t own_stream = nullptr;
+  hipStream_t side[kBatchSide] = {};  // the other groups' streams
+  hipEvent_t fork = nullptr, join[kBatchSide] = {};
   void* mem = nullptr;
+  void* draws = nullptr;         // streamed draws (NULL: regenerated)
   DevState* st = nullptr;   // [count]
   DevResult* res = nullptr; // [count]
   hipGraphExec_t graph = nullptr;
@@ -1490,8 +1496,18 @@ void batch_release(rg_batch* bt) {
   bt->graph = nullptr;
   if (bt->own_stream) (void)hipStreamDestroy(bt->own_stream);
   bt->own_stream = nullptr;
+  for (int i = 0; i < kBatchSide; ++i) {
+    if (bt->side[i]) (void)hipStreamDestroy(bt->side[i]);
+    if (bt->join[i]) (void)hipEventDestroy(bt->join[i]);
+    bt->side[i] = nullptr;
+    bt->join[i] = nullptr;
+  }
+  if (bt->fork) (void)hipEventDestroy(bt->fork);
+  bt->fork = nullptr;
   if (bt->mem) (void)hipFree(bt->mem);
   bt->mem = nullptr;
+  if (bt->draws) (void)hipFree(bt->draws);
+  bt->draws = nullptr;
   for (rg_handle* h : bt->inst) rg_destroy(h);  // no workspace of their own
   bt->inst.clear();
 }
@@ -1532,7 +1548,30 @@ int batch_ensure_memory(rg_batch* bt) {
     return bfail(bt, RG_E_NOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
   }
   if (!bt->own_stream) e = hipStreamCreateWithFlags(&bt->own_stream, hipStreamNonBlocking);
+  if (e == hipSuccess && !bt->fork) e = hipEventCreateWithFlags(&bt->fork, hipEventDisableTiming);
+  for (size_t g = 1; g < ng && g <= (size_t)kBatchSide && e == hipSuccess; ++g) {
+    if (!bt->side[g - 1]) e = hipStreamCreateWithFlags(&bt->side[g - 1], hipStreamNonBlocking);
+    if (e == hipSuccess && !bt->join[g - 1])
+      e = hipEventCreateWithFlags(&bt->join[g - 1], hipEventDisableTiming);
+  }
   if (e != hipSuccess) return bfail(bt, RG_E_HIP, std::string("batch stream: ") + hipGetErrorString(e));
+  // draw buffers, where they all fit (and in a quarter of the free memory); a
+  // batch that cannot have them regenerates its draws
+  std::vector<size_t> o_w(count), o_th(count);
+  size_t doff = 0;
+  for (int i = 0; i < count; ++i) {
+    const Problem& pr = bt->inst[i]->pr;
+    o_w[i] = doff;
+    doff = align256(doff + sizeof(float) * (size_t)pr.H * pr.p.nw * pr.s.N);
+    o_th[i] = doff;
+    doff = align256(doff + sizeof(float) * (size_t)pr.p.nth * pr.s.N);
+  }
+  size_t mfree = 0, mtotal = 0;
+  if ((double)doff <= kBatchDrawBytes && hipMemGetInfo(&mfree, &mtotal) == hipSuccess &&
+      doff <= mfree / 4 && hipMalloc(&bt->draws, doff) != hipSuccess) {
+    bt->draws = nullptr;
+    (void)hipGetLastError();
+  }
   char* base = (char*)bt->mem;
   bt->st = (DevState*)(base + o_st);
   bt->res = (DevResult*)(base + o_res);
@@ -1545,6 +1584,10 @@ int batch_ensure_memory(rg_batch* bt) {
     b.srch = srch + i;
     b.res = bt->res + i;
     b.rlist = (int2*)(base + o_rl[i]);
+    if (bt->draws) {
+      b.wbuf = (float*)((char*)bt->draws + o_w[i]);
+      b.thbuf = (float*)((char*)bt->draws + o_th[i]);
+    }
     h->b = b;
     h->ws = bt->mem;  // carved from the batch's allocation: never freed by the handle
     h->ws_owned = false;
@@ -1578,7 +1621,7 @@ int batch_ensure_memory(rg_batch* bt) {
       flat_fill_ctl(h->pr, h->b, st_c[g].data() + m * csz);
       st_rp[g][m] = h->b.res;
       st_tf[g][m] = (int32_t)st_ti[g].size();
-      const int nt = (h->pr.s.N + bt->tile - 1) / bt->tile;
+      const int tile = flat_tile(G.lanes, bt->tile), nt = (h->pr.s.N + tile - 1) / tile;
       for (int q = 0; q < nt; ++q) st_ti[g].push_back((int32_t)m);
     }
     G.args = base + o_args[g];
@@ -1599,24 +1642,80 @@ int batch_ensure_memory(rg_batch* bt) {
   return RG_OK;
 }
 
-// One batched step on stream ms.
-hipError_t batch_enqueue(rg_batch* bt, hipStream_t ms) {
-  hipError_t e = hipSuccess;
-  for (const BatchGroup& G : bt->groups)
-    if (e == hipSuccess) e = launch_flat_setup(G.kind, G.ctl, (int)G.members.size(), ms);
-  for (int r = 0; r < bt->rounds && e == hipSuccess; ++r) {
-    for (const BatchGroup& G : bt->groups)
-      if (e == hipSuccess)
-        e = launch_flat_rollout(G.kind, G.inject, G.args, G.tile_inst, G.tile_first, G.tiles,
-                                G.cmax, bt->tile, ms);
-    for (const BatchGroup& G : bt->groups)
-      if (e == hipSuccess)
-        e = launch_flat_recheck(G.kind, G.inject, G.args64, G.ctl, (int)G.members.size(), ms);
+// One group's whole step on stream gs.
+hipError_t batch_enqueue_group(const rg_batch* bt, const BatchGroup& G, hipStream_t gs) {
+  const int nm = (int)G.members.size(), rng = bt->draws ? 0 : 1;
+  hipError_t e = rng ? hipSuccess : launch_flat_gen(G.kind, G.args, nm, gs);
+  if (e == hipSuccess) e = launch_flat_setup(G.kind, G.ctl, nm, gs);
+  for (int r = 0; r < G.rounds && e == hipSuccess; ++r) {
+    e = launch_flat_rollout(G.kind, G.inject, rng, G.lanes, G.args, G.tile_inst, G.tile_first,
+                            G.tiles, G.cmax, bt->tile, gs);
+    if (e == hipSuccess) e = launch_flat_recheck(G.kind, G.inject, rng, G.args64, G.ctl, nm, gs);
   }
-  for (const BatchGroup& G : bt->groups)
-    if (e == hipSuccess)
-      e = launch_flat_finalize(G.kind, G.ctl, G.resptr, (int)G.members.size(), ms);
+  if (e == hipSuccess) e = launch_flat_finalize(G.kind, G.ctl, G.resptr, nm, gs);
   return e;
+}
+
+// One batched step on stream ms: group 0 on ms itself, the others on the side
+// streams (in turn), all between the fork and the joins.
+hipError_t batch_enqueue(rg_batch* bt, hipStream_t ms) {
+  const size_t ng = bt->groups.size();
+  const int sides = (int)std::min(ng - 1, (size_t)kBatchSide);
+  hipError_t e = hipSuccess;
+  if (sides > 0) e = hipEventRecord(bt->fork, ms);
+  for (int i = 0; i < sides && e == hipSuccess; ++i) e = hipStreamWaitEvent(bt->side[i], bt->fork, 0);
+  for (size_t g = 0; g < ng && e == hipSuccess; ++g)
+    e = batch_enqueue_group(bt, bt->groups[g], g == 0 ? ms : bt->side[(g - 1) % kBatchSide]);
+  // join also after an error, so that a capture can end
+  for (int i = 0; i < sides; ++i) {
+    hipError_t ej = hipEventRecord(bt->join[i], bt->side[i]);
+    if (ej == hipSuccess) ej = hipStreamWaitEvent(ms, bt->join[i], 0);
+    if (e == hipSuccess) e = ej;
+  }
+  return e;
+}
+
+// Rollout layout of the batch's 9-state instances: those with horizons above the
+// returned one run on groups of lanes, the others one lane per scenario.  The
+// layouts' rounds run side by side, each a rollout and an FP64 recheck: a round
+// lasts at least either layout's longest chain of steps (0.75 us a step on
+// groups, 2.6 on one lane with a second wave on its SIMD, 0.95 and 3.4 with
+// regenerated draws, 1.1 for the recheck) and the time of all work (37 and 21 ps
+// per scenario-step over the whole chip, 51 and 27 with regenerated draws, 7 and
+// 8 for the 4-state plant; about 0.6 of the horizons run, refused candidates
+// stopping early).  Chains and work fill each other's gaps only partly: the root
+// of their squares follows the measured times, and the threshold makes it least.  Batched step, half the instances
+// 9-state, N to 8192, H to 3000: 48 instances all on one lane 134 ms, all on
+// groups 107, threshold 1500 97; 128 instances 199, 207 and (2400) 143.
+int batch_group_horizon(const std::vector<rg_handle*>& inst, bool streamed) {
+  std::vector<std::pair<int, double>> hn;  // horizon, scenario-steps
+  const double live = 0.6e-6;              // ps per scenario-step -> us
+  double lq4 = 0.0;
+  for (const rg_handle* h : inst) {
+    const double steps = (double)h->pr.H * h->pr.s.N;
+    if (h->pr.p.kind == RG_PLANT_FC9) hn.push_back({h->pr.H, steps});
+    else lq4 += steps * live * (streamed ? 7.0 : 8.0);
+  }
+  std::sort(hn.begin(), hn.end());
+  const double wg = live * (streamed ? 37.0 : 51.0), w1 = live * (streamed ? 21.0 : 27.0);
+  const double cg = streamed ? 0.75 : 0.95, c1 = streamed ? 2.6 : 3.4;
+  double above = 0.0, below = 0.0, best = INFINITY;
+  for (const auto& p : hn) above += p.second;
+  int theta = 0;
+  for (size_t i = 0; i <= hn.size(); ++i) {  // the i shortest on one lane
+    if (i > 0) {
+      above -= hn[i - 1].second;
+      below += hn[i - 1].second;
+    }
+    const double chain = std::max(i > 0 ? (c1 + 1.1) * hn[i - 1].first : 0.0,
+                                  i < hn.size() ? (cg + 1.1) * hn.back().first : 0.0);
+    const double t = std::hypot(chain, above * wg + below * w1 + lq4);
+    if (t < best) {
+      best = t;
+      theta = i > 0 ? hn[i - 1].first : 0;
+    }
+  }
+  return theta;
 }
 
 }  // namespace
@@ -1685,20 +1784,29 @@ int rg_batch_create(const rg_instance_desc* descs, int32_t count, const rg_optio
     bt->inst.push_back(h);
     bt->noff.push_back(noff);
     noff += h->pr.p.n;
-    if (h->cfg.rounds > bt->rounds) bt->rounds = h->cfg.rounds;
-    // group by plant kind and injection
+  }
+  double draw_bytes = 0.0;
+  for (const rg_handle* h : bt->inst)
+    draw_bytes += 4.0 * h->pr.s.N * ((double)h->pr.H * h->pr.p.nw + h->pr.p.nth);
+  const int theta = batch_group_horizon(bt->inst, draw_bytes <= kBatchDrawBytes);
+  for (int i = 0; i < count; ++i) {  // groups: plant kind, injection, layout
+    const rg_handle* h = bt->inst[i];
+    const int lanes = h->pr.p.kind == RG_PLANT_FC9 && h->pr.H > theta ? 16 : 1;
     BatchGroup* G = nullptr;
     for (BatchGroup& g : bt->groups)
-      if (g.kind == h->pr.p.kind && g.inject == h->pr.s.inject) G = &g;
+      if (g.kind == h->pr.p.kind && g.inject == h->pr.s.inject && g.lanes == lanes) G = &g;
     if (!G) {
       bt->groups.emplace_back();
       G = &bt->groups.back();
       G->kind = h->pr.p.kind;
       G->inject = h->pr.s.inject;
+      G->lanes = lanes;
     }
     G->members.push_back(i);
-    G->tiles += (h->pr.s.N + bt->tile - 1) / bt->tile;
+    const int tile = flat_tile(lanes, bt->tile);
+    G->tiles += (h->pr.s.N + tile - 1) / tile;
     if (h->cfg.cmax_round > G->cmax) G->cmax = h->cfg.cmax_round;
+    if (h->cfg.rounds > G->rounds) G->rounds = h->cfg.rounds;
   }
   bt->t.assign(count, 0u);
   *out = bt;

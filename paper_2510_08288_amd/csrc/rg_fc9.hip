@@ -11,20 +11,19 @@ namespace rg {
 // the margins equal that kernel's bit for bit.  CKPT = 1: the checkpoint
 // candidate's groups store the adjoint's checkpoints.  CHANCE = 1: the
 // chance-constrained verdict (groups stop on their own, every margin key kept).
+// Body of one workgroup: candidate row c, scenario tile bx.
 template <class T, int RNG, int INJ, int CKPT, int CHANCE>
-__global__ void __launch_bounds__(256) k_rollout_fc9_lanes(const RollArgs<2, T> a) {
-  if (gen_rows<2>(a)) return;
+__device__ __forceinline__ void fc9_lanes_block(const RollArgs<2, T>& a, int c, int bx) {
   __shared__ unsigned long long sh[16];
   __shared__ __align__(16) T xch[4 * kWaveSlots<T>];
   DevSearch* S = a.srch;
-  const int c = blockIdx.y;
   if (S->done || c >= S->n_cand) return;  // uniform over the workgroup
   const bool ck = CKPT == 1 && c == (a.ckpt_cand >= 0 ? a.ckpt_cand : S->nk_idx);
   const int early = a.early && !S->full[c];
-  if (refused_by_steady_state(early, S, c)) return;
+  if (refused_by_steady_state(early, S, c, bx)) return;
   const GroupLane gl;
   const int wave = threadIdx.x >> 6;
-  const int k = (int)(blockIdx.x * (blockDim.x >> 6) + wave) * kWaveGroups + gl.grp;
+  const int k = (int)(bx * (blockDim.x >> 6) + wave) * kWaveGroups + gl.grp;
   const uint32_t t = a.st->t;
   const int q = CHANCE ? S->q : 0;
   const bool live = gl.grp < kWaveGroups && k < a.N;
@@ -66,6 +65,37 @@ __global__ void __launch_bounds__(256) k_rollout_fc9_lanes(const RollArgs<2, T> 
     atomicMin(&S->key_all[c], kall);
     if (kfar != ~0ull) atomicMin(&S->key_far[c], kfar);
   }
+}
+
+template <class T, int RNG, int INJ, int CKPT, int CHANCE>
+__global__ void __launch_bounds__(256) k_rollout_fc9_lanes(const RollArgs<2, T> a) {
+  if (gen_rows<2>(a)) return;
+  fc9_lanes_block<T, RNG, INJ, CKPT, CHANCE>(a, blockIdx.y, blockIdx.x);
+}
+
+// Batched serving: the FP32 form over every instance of a group (tables as
+// k_flat_rollout's).
+template <int RNG, int INJ>
+__global__ void __launch_bounds__(256)
+    k_flat_rollout_fc9_lanes(const RollArgs<2, float>* __restrict__ args,
+                             const int* __restrict__ tile_inst,
+                             const int* __restrict__ tile_first) {
+  const int i = tile_inst[blockIdx.x];
+  fc9_lanes_block<float, RNG, INJ, 0, 0>(args[i], blockIdx.y, (int)blockIdx.x - tile_first[i]);
+}
+
+hipError_t launch_flat_rollout_fc9_lanes(int inject, int rng, const void* args_dev,
+                                         const int* tile_inst, const int* tile_first, int tiles,
+                                         int cmax, int block, hipStream_t st) {
+  return by_bit(rng, [&](auto rc) {
+    constexpr int R = decltype(rc)::value;
+    return by_bit(inject, [&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      hipLaunchKernelGGL((k_flat_rollout_fc9_lanes<R, I>), dim3(tiles, cmax), dim3(block), 0, st,
+                         (const RollArgs<2, float>*)args_dev, tile_inst, tile_first);
+      return hipGetLastError();
+    });
+  });
 }
 
 hipError_t launch_rollout_fc9_lanes(const Problem& pr, double band, int precision, int early_exit,

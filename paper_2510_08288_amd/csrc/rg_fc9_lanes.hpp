@@ -261,6 +261,9 @@ hipError_t launch_rollout_fc9_lanes(const Problem& pr, double band, int precisio
                                     int record, const LaunchCfg& cfg, const DevBuffers& b,
                                     hipStream_t st, int ckpt_cand, int Kc, int gen_rows,
                                     float* gen_w, float* gen_th);
+hipError_t launch_flat_rollout_fc9_lanes(int inject, int rng, const void* args_dev,
+                                         const int* tile_inst, const int* tile_first, int tiles,
+                                         int cmax, int block, hipStream_t st);
 // Scenarios of one workgroup of `block` threads.
 static inline int fc9_lanes_per_block(int block) { return block / 64 * kWaveGroups; }
 

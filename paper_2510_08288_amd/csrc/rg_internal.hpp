@@ -285,19 +285,24 @@ hipError_t launch_grad_reduce(const DevBuffers& b, int max_entries, int nth, int
 hipError_t launch_eval_tanh64(const double* x_dev, double* y_dev, int n, hipStream_t st);
 size_t flat_args_size(int kind);
 void flat_fill_args(const Problem& pr, double band, int early, const DevBuffers& b, void* out);
-hipError_t launch_flat_rollout(int kind, int inject, const void* args_dev, const int* tile_inst,
-                               const int* tile_first, int tiles, int cmax, int block,
-                               hipStream_t st);
+// rng: 0 streamed draws (launch_flat_gen fills the instances' buffers), 1
+// regenerated; lanes: 1, or 16 (9-state plant, groups of lanes).
+hipError_t launch_flat_rollout(int kind, int inject, int rng, int lanes, const void* args_dev,
+                               const int* tile_inst, const int* tile_first, int tiles, int cmax,
+                               int block, hipStream_t st);
+hipError_t launch_flat_gen(int kind, const void* args_dev, int count, hipStream_t st);
+// Scenarios of one rollout workgroup of `block` threads.
+int flat_tile(int lanes, int block);
 // FP64 recheck argument blocks and control blocks of the instances, and the
-// flat launches over a group: recheck + decision (one workgroup per instance),
+// flat launches over a group: recheck + decision (some workgroups per instance),
 // round-0 setup (one workgroup per instance), result records (res_dev: the
 // instances' result record addresses, device array).
 size_t flat_args64_size(int kind);
 size_t flat_ctl_size(int kind);
 void flat_fill_args64(const Problem& pr, int early, const DevBuffers& b, void* out);
 void flat_fill_ctl(const Problem& pr, const DevBuffers& b, void* out);
-hipError_t launch_flat_recheck(int kind, int inject, const void* args64_dev, const void* ctl_dev,
-                               int count, hipStream_t st);
+hipError_t launch_flat_recheck(int kind, int inject, int rng, const void* args64_dev,
+                               const void* ctl_dev, int count, hipStream_t st);
 hipError_t launch_flat_setup(int kind, const void* ctl_dev, int count, hipStream_t st);
 hipError_t launch_flat_finalize(int kind, const void* ctl_dev, DevResult* const* res_dev, int count,
                                 hipStream_t st);

@@ -66,7 +66,7 @@ template <int KIND>
 __device__ void decide_body(const typename Plant<KIND, double>::Coef& pc, const DevState* st,
                             DevSearch* S, const DevGrad* grad);
 template <int KIND>
-__device__ void last_block_decides(const CtlArgs<KIND>& ctl);
+__device__ void last_block_decides(const CtlArgs<KIND>& ctl, uint32_t blocks);
 template <int KIND>
 __device__ void true_plant_step(const RollArgs<KIND, double>& a, const double* x_in, double v,
                                 uint32_t t, double* x_out);
@@ -420,18 +420,30 @@ __global__ void __launch_bounds__(256) k_rollout(const RollArgs<KIND, T> a) {
 }
 
 // Batched serving: one launch per search round covers every instance of a
-// (plant, disturbance injection) group.  Workgroup g of the flat grid takes
-// scenario tile g - tile_first[i] of instance i = tile_inst[g], with the
-// instance's own argument block from device memory; row blockIdx.y is the
-// candidate (instances with fewer candidates in the round return at once).
-// FP32, robust verdict, draws regenerated in the lanes.
-template <int KIND, int INJ>
+// group.  Workgroup g of the flat grid takes scenario tile g - tile_first[i] of
+// instance i = tile_inst[g], with the instance's own argument block from device
+// memory; row blockIdx.y is the candidate (instances with fewer candidates in
+// the round return at once).  FP32, robust verdict, one lane per scenario.
+template <int KIND, int RNG, int INJ>
 __global__ void __launch_bounds__(256) k_flat_rollout(const RollArgs<KIND, float>* __restrict__ args,
                                                       const int* __restrict__ tile_inst,
                                                       const int* __restrict__ tile_first) {
   __shared__ unsigned long long sh[16];
   const int i = tile_inst[blockIdx.x];
-  rollout_block<KIND, float, 1, INJ, 0, 0>(args[i], blockIdx.y, (int)blockIdx.x - tile_first[i], sh);
+  rollout_block<KIND, float, RNG, INJ, 0, 0>(args[i], blockIdx.y, (int)blockIdx.x - tile_first[i],
+                                             sh);
+}
+
+// Batched serving with streamed draws: this step's draws of every instance of a
+// group (blockIdx.y) into its buffers.
+template <int KIND>
+__global__ void __launch_bounds__(256) k_flat_gen(const RollArgs<KIND, float>* __restrict__ args) {
+  const RollArgs<KIND, float>& a = args[blockIdx.y];
+  const size_t work = (size_t)a.H * a.N + (Plant<KIND, float>::nth > 0 ? (size_t)a.N : 0);
+  const uint32_t t = a.st->t;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < work;
+       i += (size_t)gridDim.x * blockDim.x)
+    gen_body<KIND>(a, const_cast<float*>(a.wbuf), const_cast<float*>(a.thbuf), i, t, true);
 }
 
 // ---------------------------------------------------------------------------
@@ -878,7 +890,7 @@ __global__ void __launch_bounds__(256, 2) k_recheck_lq4_mx(const RollArgs<1, dou
       }
     }
   }
-  if (decide) last_block_decides<1>(ctl);
+  if (decide) last_block_decides<1>(ctl, gridDim.x);
 }
 
 // FP64 re-simulation of the near-band list, 9-state plant (one entry per group
@@ -894,50 +906,44 @@ __global__ void __launch_bounds__(64) k_recheck_fc9(const RollArgs<2, double> a,
                               xch + gl.grp * kGroupStride<double>,
                               (int)blockIdx.x * kWaveGroups + gl.grp,
                               (int)gridDim.x * kWaveGroups);
-  if (decide) last_block_decides<2>(ctl);
+  if (decide) last_block_decides<2>(ctl, gridDim.x);
 }
 
 // Batched serving: the FP64 recheck of every instance of a group in one launch,
-// one workgroup per instance (its own near-band list, as k_recheck), which then
-// takes that instance's decision for the round (as the last workgroup of
-// k_recheck does).  The workgroup's own rechecks are published by a
-// device-scope fence before the decision reads the verdicts.
-template <int KIND, int INJ>
+// gridDim.y workgroups per instance (its own near-band list, as the other
+// rechecks), the last of which takes that instance's decision for the round.
+template <int KIND, int RNG, int INJ>
 __global__ void __launch_bounds__(64) k_flat_recheck(const RollArgs<KIND, double>* __restrict__ args,
                                                      const CtlArgs<KIND>* __restrict__ ctl) {
   const RollArgs<KIND, double>& a = args[blockIdx.x];
   DevSearch* S = a.srch;
-  if (S->done) return;  // uniform: nothing writes it before the decision below
+  if (S->done) return;  // uniform: nothing writes it before every workgroup has counted itself
   const int n = S->n_recheck;
   const uint32_t t = a.st->t;
   if constexpr (KIND == 2) {
     __shared__ __align__(16) double xch[kWaveSlots<double>];
     const GroupLane gl;
-    recheck_fc9_lanes<1, INJ>(a, S, n, t, gl, xch + gl.grp * kGroupStride<double>, gl.grp,
-                              kWaveGroups);
-    __threadfence();
-    __syncthreads();
-    const CtlArgs<KIND>& cl = ctl[blockIdx.x];
-    decide_body<KIND>(cl.pc, cl.st, cl.srch, cl.grad);
-    return;
+    recheck_fc9_lanes<RNG, INJ>(a, S, n, t, gl, xch + gl.grp * kGroupStride<double>,
+                                (int)blockIdx.y * kWaveGroups + gl.grp,
+                                (int)gridDim.y * kWaveGroups);
+  } else {
+    for (int i = (int)(blockIdx.y * blockDim.x + threadIdx.x); i < n;
+         i += (int)(gridDim.y * blockDim.x)) {
+      const int2 e = a.rlist[i];
+      const int c = e.x, k = e.y;
+      if (a.early &&
+          (__hip_atomic_load(&S->dead[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
+           __hip_atomic_load(&S->fail64[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+        continue;
+      int jb = 0, ns = 0;
+      const double m = rollout_lane<KIND, double, RNG, INJ>(
+          a, a.early, S->v[c], k, t, a.early ? &S->fail64[c] : nullptr, jb, ns, nullptr);
+      atomicMin(&S->key64[c], ord64(m));
+      if (m < 0.0)
+        __hip_atomic_store(&S->fail64[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const int2 e = a.rlist[i];
-    const int c = e.x, k = e.y;
-    if (a.early &&
-        (__hip_atomic_load(&S->dead[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-         __hip_atomic_load(&S->fail64[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-      continue;
-    int jb = 0, ns = 0;
-    const double m = rollout_lane<KIND, double, 1, INJ>(
-        a, a.early, S->v[c], k, t, a.early ? &S->fail64[c] : nullptr, jb, ns, nullptr);
-    atomicMin(&S->key64[c], ord64(m));
-    if (m < 0.0) __hip_atomic_store(&S->fail64[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __threadfence();
-  __syncthreads();
-  const CtlArgs<KIND>& cl = ctl[blockIdx.x];
-  decide_body<KIND>(cl.pc, cl.st, cl.srch, cl.grad);
+  last_block_decides<KIND>(ctl[blockIdx.x], gridDim.y);
 }
 
 // Batched serving: round-0 setup of every instance of a group, one workgroup
@@ -1735,13 +1741,13 @@ __global__ void __launch_bounds__(128) k_decide(const CtlArgs<KIND> a) {
 // them, resets the count for the next launch and runs the decision.  No
 // workgroup waits for another.
 template <int KIND>
-__device__ void last_block_decides(const CtlArgs<KIND>& ctl) {
+__device__ void last_block_decides(const CtlArgs<KIND>& ctl, uint32_t blocks) {
   __shared__ int s_last;
   __syncthreads();
   if (threadIdx.x == 0) {
     __threadfence();
     const uint32_t prev = atomicAdd(&ctl.srch->blocks_done, 1u);
-    s_last = (prev == gridDim.x - 1) ? 1 : 0;
+    s_last = (prev == blocks - 1) ? 1 : 0;
   }
   __syncthreads();
   if (!s_last) return;
@@ -3077,16 +3083,30 @@ void flat_fill_ctl(const Problem& pr, const DevBuffers& b, void* out) {
   }
 }
 
-hipError_t launch_flat_recheck(int kind, int inject, const void* args64_dev, const void* ctl_dev,
-                               int count, hipStream_t st) {
+hipError_t launch_flat_recheck(int kind, int inject, int rng, const void* args64_dev,
+                               const void* ctl_dev, int count, hipStream_t st) {
+  // workgroups per instance: 9-state entries are long and seven to a workgroup
+  const dim3 grid(count, kind == 2 ? 8 : 2);
   return by_kind(kind, [&](auto kc) {
     constexpr int K = decltype(kc)::value;
-    return by_bit(inject, [&](auto ic) {
-      constexpr int I = decltype(ic)::value;
-      hipLaunchKernelGGL((k_flat_recheck<K, I>), dim3(count), dim3(64), 0, st,
-                         (const RollArgs<K, double>*)args64_dev, (const CtlArgs<K>*)ctl_dev);
-      return hipGetLastError();
+    return by_bit(rng, [&](auto rc) {
+      constexpr int R = decltype(rc)::value;
+      return by_bit(inject, [&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        hipLaunchKernelGGL((k_flat_recheck<K, R, I>), grid, dim3(64), 0, st,
+                           (const RollArgs<K, double>*)args64_dev, (const CtlArgs<K>*)ctl_dev);
+        return hipGetLastError();
+      });
     });
+  });
+}
+
+hipError_t launch_flat_gen(int kind, const void* args_dev, int count, hipStream_t st) {
+  return by_kind(kind, [&](auto kc) {
+    constexpr int K = decltype(kc)::value;
+    hipLaunchKernelGGL(k_flat_gen<K>, dim3(256, count), dim3(256), 0, st,
+                       (const RollArgs<K, float>*)args_dev);
+    return hipGetLastError();
   });
 }
 
@@ -3108,20 +3128,28 @@ hipError_t launch_flat_finalize(int kind, const void* ctl_dev, DevResult* const*
   });
 }
 
-hipError_t launch_flat_rollout(int kind, int inject, const void* args_dev, const int* tile_inst,
-                               const int* tile_first, int tiles, int cmax, int block,
-                               hipStream_t st) {
+hipError_t launch_flat_rollout(int kind, int inject, int rng, int lanes, const void* args_dev,
+                               const int* tile_inst, const int* tile_first, int tiles, int cmax,
+                               int block, hipStream_t st) {
+  if (lanes == 16)
+    return launch_flat_rollout_fc9_lanes(inject, rng, args_dev, tile_inst, tile_first, tiles, cmax,
+                                         block, st);
   const dim3 grid(tiles, cmax);
   return by_kind(kind, [&](auto kc) {
     constexpr int K = decltype(kc)::value;
-    return by_bit(inject, [&](auto ic) {
-      constexpr int I = decltype(ic)::value;
-      hipLaunchKernelGGL((k_flat_rollout<K, I>), grid, dim3(block), 0, st,
-                         (const RollArgs<K, float>*)args_dev, tile_inst, tile_first);
-      return hipGetLastError();
+    return by_bit(rng, [&](auto rc) {
+      constexpr int R = decltype(rc)::value;
+      return by_bit(inject, [&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        hipLaunchKernelGGL((k_flat_rollout<K, R, I>), grid, dim3(block), 0, st,
+                           (const RollArgs<K, float>*)args_dev, tile_inst, tile_first);
+        return hipGetLastError();
+      });
     });
   });
 }
+
+int flat_tile(int lanes, int block) { return lanes == 16 ? fc9_lanes_per_block(block) : block; }
 
 hipError_t launch_trajectory(const Problem& pr, double v, const int32_t* k_list_dev, int nk,
                              int precision, double* traj_dev, const DevBuffers& b,

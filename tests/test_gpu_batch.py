@@ -130,3 +130,31 @@ def test_batch_autotune_keeps_kappa(R, oracle_mod):
     kb = [b.step(xs, rs, vps, use_graph=True)["kappa"] for _ in range(3)]
     b.close()
     assert all(np.array_equal(x, y) for x, y in zip(ka, kb))
+
+
+def test_layouts_and_draw_modes_agree(R):
+    # 9-state horizons far enough apart that some instances run on groups of lanes and some one
+    # lane per scenario, both injections, beside 4-state ones; then a batch whose draws exceed
+    # what a batch keeps (they are regenerated): kappa of every instance as a single governor's
+    probs = [W.fc9_problem(N=900, H=40, dt=0.005, scen_seed=5, instance=1),
+             W.fc9_problem(N=300, H=700, dt=0.005, scen_seed=6, instance=2),
+             W.fc9_problem(N=2500, H=60, dt=0.005, scen_seed=7, instance=3,
+                           inject=W.INJECT_POST, w_half=1e-4),
+             W.fc9_problem(N=31, H=650, dt=0.005, scen_seed=8, instance=4,
+                           inject=W.INJECT_POST, w_half=1e-4),
+             W.lq4_problem(seed=24, N=257, H=203, dt=0.01, eps=0.01, instance=5)]
+    g0 = R.Governor(probs[0])
+    eq = g0.equilibrium(0.5)
+    for group in (probs, [W.fc9_problem(N=140000, H=3600, dt=0.002)]):
+        xs = [eq if p.kind == W.PLANT_FC9 else np.zeros(4) for p in group]
+        vs = [0.5 if p.kind == W.PLANT_FC9 else 0.0 for p in group]
+        b = R.Batch(group)
+        for t in range(2 if len(group) > 1 else 1):
+            rs = [1.9 - 0.6 * t if p.kind == W.PLANT_FC9 else 1.5 - 2.5 * t for p in group]
+            out = b.step(xs, rs, vs)
+            for i, p in enumerate(group):
+                g = R.Governor(p, rng_mode=R.RNG_INLINE)
+                g.set_step(t)
+                assert g.step(xs[i], rs[i], vs[i])["kappa"] == out["kappa"][i], (t, i)
+                g.close()
+        b.close()
