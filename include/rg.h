@@ -148,7 +148,10 @@ typedef struct rg_options {
     double band;           /* recheck band on |FP32 margin| (default 1e-4) */
     int32_t K;             /* halvings after the kappa = 1 probe (default 12) */
     int32_t search;        /* enum rg_search (default BISECT) */
-    int32_t depth;         /* bisection levels evaluated per device round (1..6; 0 = auto) */
+    int32_t depth;         /* bisection levels evaluated per device round (1..6; 0 = auto:
+                              from the problem's size, and later rounds may follow the
+                              bisection path to the root predicted from the margins so
+                              far instead; the result is the same) */
     int32_t M;             /* grid points for RG_SEARCH_GRID (2..127) */
     int32_t refine;        /* halvings after the grid */
     int32_t early_exit;    /* 1: a candidate stops once one lane is below -band */
@@ -437,7 +440,8 @@ int rg_equilibrium(rg_handle* h, double v, double* x_out);
  * flat rollout launch (all their scenario tiles in one grid, FP32, one lane per
  * scenario, or for the longest horizons of the 9-state plant a group of lanes),
  * then their FP64 rechecks and decisions.  All instances
- * use one search depth (opt.depth = 0: from the sum of N over the batch; large
+ * use one search depth (opt.depth = 0: from the sum of N over the batch, and
+ * rounds along the predicted bisection path; large
  * batches evaluate one candidate per round).  opt: precision F32_RECHECK,
  * search BISECT or GRID, chance_q 0 (else RG_E_NOTSUP); block is the scenario
  * tile (64, 128, 256); predict as for rg_create; persistent_wgs is accepted

@@ -26,6 +26,8 @@ struct rg_handle {
   LaunchCfg cfg;
   bool auto_depth = false;  // opt.depth was left to the library
   int pred_tree = 0;        // tree levels of a predicted round 0
+  int batch_path = 0;       // batch member: candidates of a round along the predicted path
+  int path = 0;             // the same, as planned (0: trees only)
   // device memory
   hipStream_t stream = nullptr;
   void* ws = nullptr;
@@ -284,6 +286,17 @@ void plan(rg_handle* h) {
       c.rounds = 1 + (h->opt.K + d - 1) / d;
     }
   }
+  // Rounds along the predicted path (decide_body), where the depth is the
+  // library's: as many candidates as the workspace holds anyway.  A grid's
+  // refinement takes one more round, so that one guess may be wrong (bisection
+  // has it: round 0 counts no level).
+  h->path = h->batch_path;
+  if (h->auto_depth && h->opt.search == RG_SEARCH_BISECT && h->opt.predict) h->path = h->opt.K;
+  if (h->auto_depth && h->opt.search == RG_SEARCH_GRID && h->opt.refine > d) {
+    h->path = std::min(h->opt.refine, c.cmax_round);
+    c.rounds += 1;
+  }
+  if (h->batch_path > c.cmax_round) c.cmax_round = h->batch_path;
   h->cfg = c;
   // a probe-only round 0 holds the probe and the probes of the next steps
   const int sp = spec_allowed(h);
@@ -306,6 +319,8 @@ void fill_search(const rg_handle* h, DevSearch* S, int32_t spec_depth, int32_t s
   S->K = h->opt.K;
   S->depth = h->opt.depth;
   S->pred_tree = h->pred_tree;
+  S->path = h->path;
+  S->max_rounds = h->cfg.rounds;
   S->M = h->opt.M;
   S->refine = h->opt.refine;
   S->precision = h->opt.precision;
@@ -1246,9 +1261,11 @@ int reset_search_schedule(rg_handle* h) {
                              sizeof(predict), hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, hipMemcpyAsync((char*)h->b.srch + offsetof(DevSearch, pred), &none, sizeof(none),
                              hipMemcpyHostToDevice, h->stream));
-    const int32_t pred_tree = h->pred_tree;
-    HIPCHK(h, hipMemcpyAsync((char*)h->b.srch + offsetof(DevSearch, pred_tree), &pred_tree,
-                             sizeof(pred_tree), hipMemcpyHostToDevice, h->stream));
+    const int32_t tree[3] = {h->pred_tree, h->path, h->cfg.rounds};  // pred_tree, path, max_rounds
+    static_assert(offsetof(DevSearch, max_rounds) == offsetof(DevSearch, pred_tree) + 8,
+                  "the round plan's fields are adjacent");
+    HIPCHK(h, hipMemcpyAsync((char*)h->b.srch + offsetof(DevSearch, pred_tree), tree, sizeof(tree),
+                             hipMemcpyHostToDevice, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
   }
   return RG_OK;
@@ -1718,6 +1735,9 @@ int batch_group_horizon(const std::vector<rg_handle*>& inst, bool streamed) {
   return theta;
 }
 
+// Candidates of a batch round along the predicted path.
+constexpr int kBatchPath = 8;
+
 }  // namespace
 
 extern "C" {
@@ -1780,6 +1800,10 @@ int rg_batch_create(const rg_instance_desc* descs, int32_t count, const rg_optio
       batch_release(bt);
       delete bt;
       return bfail(nullptr, rc, m);
+    }
+    if (o.depth == 0) {
+      h->batch_path = std::min(goal, kBatchPath);
+      plan(h);
     }
     bt->inst.push_back(h);
     bt->noff.push_back(noff);

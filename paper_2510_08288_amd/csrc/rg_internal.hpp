@@ -79,6 +79,12 @@ struct DevSearch {
   int32_t predict;                    // 1: enabled
   double pred;                        // previous step's kappa (NaN: none yet)
   int32_t pred_tree;                  // levels of the tree that round 0 also evaluates (0: none)
+  // Later rounds along the bisection path to the root predicted from the two
+  // largest admitted candidates (the bracket's low end and lo2, NaN: none yet,
+  // with its worst margin): at most path candidates (0: trees only), within
+  // max_rounds rounds whatever the guess
+  int32_t path, max_rounds;
+  double lo2, lo2_w;
   // Workgroups of the current recheck launch that have finished; the last one
   // takes the round's decision and resets the count.
   uint32_t blocks_done;
