@@ -48,15 +48,25 @@ __device__ __forceinline__ double dpp_row(double x) {
   return dpp64<CTRL>(x);
 }
 
-// 9-state plant: a copy of the coupling matrix W in vector registers (identity
-// DPP moves make the copies lane values), which the derivative then reads: 81
-// uniform values beside the other coefficients exceed the scalar registers, and
-// spilled scalars are restored at every use (a sixth of the one-lane FP32 loop).
-template <int KIND, class T, class Coef, class Lane>
+// 9-state plant: a copy of the first NV entries of the coupling matrix W in vector
+// registers (identity DPP moves make the copies lane values), which the derivative
+// then reads: 81 uniform values beside the other coefficients exceed the scalar
+// registers, and spilled scalars are restored at every use (a sixth of the
+// one-lane FP32 loop).  A scalar operand makes an FP32 instruction 1.8 ns long
+// instead of 1.2 to 1.4 (SIMDs full), but each vector register spared counts
+// too: with 36 entries (and the next step's draws loaded over this step's) the
+// FP32 rollouts fit 168 registers, three waves per SIMD, and a full-horizon step
+// takes 1.29 us per wave and SIMD against 1.45 with all 81 and two waves (30
+// entries 1.34, 42 1.36, none and four waves 1.38).  The batched rollouts, one
+// wave per workgroup, are no faster with three and keep all 81.
+constexpr int kVgprW = 36;
+template <int KIND>
+constexpr int kRollWaves = KIND == 2 ? 3 : 1;
+template <int KIND, int NV, class T, class Coef, class Lane>
 __device__ __forceinline__ void w_in_vgprs(const Coef& pc, T* wv, Lane& L) {
   if constexpr (KIND == 2) {
 #pragma unroll
-    for (int c = 0; c < 81; ++c) wv[c] = dpp_row<0xE4>(pc.W[c]);
+    for (int c = 0; c < 81; ++c) wv[c] = c < NV ? dpp_row<0xE4>(pc.W[c]) : pc.W[c];
     L.W = wv;
   }
 }
@@ -82,7 +92,7 @@ __device__ void true_plant_step(const RollArgs<KIND, double>& a, const double* x
 // for the other waves (which read it every 8 steps).  Without WAVE, lanes
 // stop on their own and stop_flag is only read.
 template <int KIND, class T, int RNG, int INJ, class A, int CKPT = 0, bool WAVE = false,
-          bool WREG = false>
+          int WREG = 0>
 __device__ __forceinline__ T rollout_lane(const A& a, int early, T v, int k, uint32_t t,
                                           int32_t* stop_flag, int& jbest, int& nsteps,
                                           double* traj, bool ck = false,
@@ -103,9 +113,11 @@ __device__ __forceinline__ T rollout_lane(const A& a, int early, T v, int k, uin
   }
   typename P::Lane L;
   P::lane_init(a.pc, th, v, L);
-  // WREG (the FP32 rollout kernels): W in vector registers
-  T wv[KIND == 2 && WREG ? 81 : 1];
-  if constexpr (WREG) w_in_vgprs<KIND>(a.pc, wv, L);
+  // WREG (the FP32 rollout kernels): entries of W in vector registers.  LATE: the
+  // next step's draws are loaded once this step's are used up
+  constexpr bool LATE = INJ == 0 && KIND == 2 && WREG == kVgprW;
+  T wv[KIND == 2 && WREG > 0 ? 81 : 1];
+  if constexpr (WREG > 0) w_in_vgprs<KIND, WREG>(a.pc, wv, L);
   T x[P::n];
 #pragma unroll
   for (int i = 0; i < P::n; ++i) x[i] = (T)a.st->x[i];
@@ -138,7 +150,7 @@ __device__ __forceinline__ T rollout_lane(const A& a, int early, T v, int k, uin
   int j = 0;
   int stop_seen = 0;  // dead flag read at the start of an 8-step block, tested at its end
   for (; j < a.H; ++j) {
-    if (j + 1 < a.H) load(j + 1, wn);
+    if (!LATE && j + 1 < a.H) load(j + 1, wn);
     if (WAVE && early && (j & 7) == 0)
       stop_seen = __hip_atomic_load(stop_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     T s[P::n];
@@ -147,6 +159,7 @@ __device__ __forceinline__ T rollout_lane(const A& a, int early, T v, int k, uin
 #pragma unroll
       for (int c = 0; c < P::nw; ++c) wt[c] = (T)wc[c];
       P::force(a.pc, L, wt, s);
+      if (LATE && j + 1 < a.H) load(j + 1, wc);
     } else {
       P::force0(a.pc, L, s);
     }
@@ -201,8 +214,10 @@ __device__ __forceinline__ T rollout_lane(const A& a, int early, T v, int k, uin
         }
       }
     }
+    if (!LATE) {
 #pragma unroll
-    for (int c = 0; c < P::nw; ++c) wc[c] = wn[c];
+      for (int c = 0; c < P::nw; ++c) wc[c] = wn[c];
+    }
   }
   nsteps = j;
   bool finite = true;
@@ -349,7 +364,7 @@ __device__ __forceinline__ float rollout_lane_tan(const A& a, float v, int k, ui
 // rollout body only (two bodies double the 9-state kernel's registers).
 // Body of one rollout workgroup: candidate row c, scenario tile bx (scenarios
 // bx * blockDim.x + threadIdx.x).
-template <int KIND, class T, int RNG, int INJ, int CKPT, int CHANCE>
+template <int KIND, class T, int RNG, int INJ, int CKPT, int CHANCE, int WREG>
 __device__ __forceinline__ void rollout_block(const RollArgs<KIND, T>& a, const int c,
                                               const int bx, unsigned long long* sh) {
   DevSearch* S = a.srch;
@@ -377,13 +392,11 @@ __device__ __forceinline__ void rollout_block(const RollArgs<KIND, T>& a, const 
       }
     } else if constexpr (CHANCE) {
       // a violating lane stops alone; the candidate dies once more than q did
-      m = rollout_lane<KIND, T, RNG, INJ, RollArgs<KIND, T>, CKPT, false,
-                       std::is_same<T, float>::value>(
+      m = rollout_lane<KIND, T, RNG, INJ, RollArgs<KIND, T>, CKPT, false, WREG>(
           a, early, (T)S->v[c], k, t, early ? &S->dead[c] : nullptr, jb, ns, nullptr, ck);
       a.per_key[(size_t)c * a.N + k] = ord64((double)m);
     } else {
-      m = rollout_lane<KIND, T, RNG, INJ, RollArgs<KIND, T>, CKPT, true,
-                       std::is_same<T, float>::value>(
+      m = rollout_lane<KIND, T, RNG, INJ, RollArgs<KIND, T>, CKPT, true, WREG>(
           a, early, (T)S->v[c], k, t, &S->dead[c], jb, ns, nullptr, ck, &stopped);
     }
     if (a.record) {
@@ -413,10 +426,11 @@ __device__ __forceinline__ void rollout_block(const RollArgs<KIND, T>& a, const 
 }
 
 template <int KIND, class T, int RNG, int INJ, int CKPT, int CHANCE = 0>
-__global__ void __launch_bounds__(256) k_rollout(const RollArgs<KIND, T> a) {
+__global__ void __launch_bounds__(256, CKPT == 2 ? 1 : kRollWaves<KIND>)
+    k_rollout(const RollArgs<KIND, T> a) {
   if (gen_rows<KIND>(a)) return;
   __shared__ unsigned long long sh[16];
-  rollout_block<KIND, T, RNG, INJ, CKPT, CHANCE>(a, blockIdx.y, blockIdx.x, sh);
+  rollout_block<KIND, T, RNG, INJ, CKPT, CHANCE, CKPT == 2 ? 81 : kVgprW>(a, blockIdx.y, blockIdx.x, sh);
 }
 
 // Batched serving: one launch per search round covers every instance of a
@@ -430,7 +444,7 @@ __global__ void __launch_bounds__(256) k_flat_rollout(const RollArgs<KIND, float
                                                       const int* __restrict__ tile_first) {
   __shared__ unsigned long long sh[16];
   const int i = tile_inst[blockIdx.x];
-  rollout_block<KIND, float, RNG, INJ, 0, 0>(args[i], blockIdx.y, (int)blockIdx.x - tile_first[i],
+  rollout_block<KIND, float, RNG, INJ, 0, 0, 81>(args[i], blockIdx.y, (int)blockIdx.x - tile_first[i],
                                              sh);
 }
 
@@ -2194,7 +2208,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
   typename P::Lane Ln;
   P::lane_init(a.pc, th, v, Ln);
   float wv[KIND == 2 ? 81 : 1];
-  w_in_vgprs<KIND>(a.pc, wv, Ln);
+  w_in_vgprs<KIND, 81>(a.pc, wv, Ln);
   const float* wb = RNG == 0 ? step_w(a, t) : nullptr;
   auto load_w = [&](int j, float* w) {
     if (RNG == 0) {
