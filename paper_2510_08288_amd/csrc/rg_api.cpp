@@ -232,10 +232,12 @@ int depth_for(const rg_handle* h, int lanes) {
   if (h->opt.depth > 0) return h->opt.depth;  // the caller's, or already resolved
   // As many levels as keep a round's waves within the budget, two at least (half
   // of the extra candidates die early: 4-state N = 16384 H = 1000 depth 1 / 2 /
-  // 3: 1.71 / 1.65 / 1.92 ms), then the smallest depth that needs no more rounds.
+  // 3: 1.71 / 1.65 / 1.92 ms; above 2^17 scenarios one, so that the recheck list
+  // of an unpredicted search stays within the allocation-free step's scratch up to
+  // 2^19 of them), then the smallest depth that needs no more rounds.
   const int goal = h->opt.search == RG_SEARCH_GRID ? h->opt.refine : h->opt.K;
   const double per_cand = waves_per_candidate(h, lanes), budget = wave_budget(h, lanes);
-  int dmax = 2;
+  int dmax = h->pr.s.N <= (1 << 17) ? 2 : 1;
   while (dmax < 6 && ((1 << (dmax + 1)) - 1) * per_cand <= budget) ++dmax;
   if (goal <= 0) return 1;
   const int rounds = (goal + dmax - 1) / dmax;

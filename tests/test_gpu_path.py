@@ -63,3 +63,14 @@ def test_batch(R, oracle_mod):
         for i, p in enumerate(probs):
             ref = oracle_mod.Oracle(p).bisect(x, r, v, t, 20)
             assert (out["kappa"][i], out["bisect_passes"][i]) == (ref["kappa"], ref["passes"]), (t, i)
+
+
+@pytest.mark.parametrize("N,search,M", [(200000, 0, 64), (500000, 0, 64), (500000, 1, 2)])
+def test_allocation_free_step_at_its_scratch_limit(R, N, search, M):
+    # without prediction a round of one level holds two candidates at most: 8 B x 2 N of the 8 MiB
+    p = W.lq4_problem(seed=W.LQ4_PLANT_SEED, N=N, H=3, dt=0.03, eps=W.LQ4_EPS)
+    g = R.Governor(p, predict=False, search=search, M=M)
+    x, r, v = _updates(1)[0]
+    a = g.step_noalloc(x, r, v)
+    g.set_step(0)
+    assert a["kappa"] == g.step(x, r, v)["kappa"]
