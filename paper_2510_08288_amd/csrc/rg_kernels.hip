@@ -28,24 +28,12 @@ __global__ void __launch_bounds__(256) k_gen(RollArgs<KIND, float> a, float* wbu
   gen_body<KIND>(a, wbuf, thbuf, (size_t)blockIdx.x * blockDim.x + threadIdx.x, a.st->t + t_ofs);
 }
 
-// A float or double moved between lanes by DPP (CTRL: quad permutations, row
-// shifts), 0 where the source lane lies outside the row.
+// A float moved between lanes by DPP (CTRL: quad permutations, row shifts), 0
+// where the source lane lies outside the row.
 template <int CTRL>
 __device__ __forceinline__ float dpp_row(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL,
                                                                0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp64(double x) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-  return __builtin_bit_cast(double, ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_row(double x) {
-  return dpp64<CTRL>(x);
 }
 
 // 9-state plant: a copy of the first NV entries of the coupling matrix W in vector
@@ -228,7 +216,7 @@ __device__ __forceinline__ T rollout_lane(const A& a, int early, T v, int k, uin
 }
 
 // The FP64 recheck of near-band entries [g0, n) with stride gstride over
-// groups of 9 lanes (rollout_fc9_lanes), with the verdict updates of k_recheck
+// groups of 9 lanes (rollout_fc9_lanes), with the verdict updates of k_recheck_lq4_mx
 // made by the group's first lane.  Lane 63 of each wave (no group) passes by.
 template <int RNG, int INJ>
 __device__ void recheck_fc9_lanes(const RollArgs<2, double>& a, DevSearch* S, int n, uint32_t t,
