@@ -52,8 +52,8 @@ PEAK_FP32_NONPACKED_TFLOPS = 78.6
 # this bench, each scaled by the counter's reading for a device copy of known size;
 # valid only for the kernel sources they were taken on (SHA-1 of the device sources
 # below, concatenated in this order).
-KERNEL_SOURCES = ("rg_kernels.hip", "rg_device.hpp", "rg_internal.hpp")
-HBM_TRAFFIC = {"kernels_sha1": "c1d43d815060d5efe28c0b2f2e2ddf994d19b6f6", "bytes_per_launch": 110040372}
+KERNEL_SOURCES = ("rg_kernels.hip", "rg_device.hpp", "rg_internal.hpp", "rg_roll.hpp")
+HBM_TRAFFIC = {"kernels_sha1": "ee1417e8c85a01a61a6366012bec829c971c2dc6", "bytes_per_launch": 110416896}
 FIXTURE = os.path.join(ROOT, "tests", "golden", "lq4_closed_loop_n4096_h2000.txt")
 
 
