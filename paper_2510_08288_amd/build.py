@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librg.so")
-SOURCES = ["rg_kernels.hip", "rg_lq4.hip", "rg_lq4_mf.hip", "rg_fc9.hip", "rg_fc9_adj.hip", "rg_async.hip", "rg_api.cpp"]
+SOURCES = ["rg_kernels.hip", "rg_lq4.hip", "rg_lq4_sweep.hip", "rg_fc9.hip", "rg_fc9_adj.hip", "rg_async.hip", "rg_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed FP32 instructions are switched off for every HIP translation unit.

@@ -482,6 +482,8 @@ struct QuadLane {
 // Row q of f(x) = s + A x + G (x.*x), summed over the quad.  Lane q forms
 // x_q's contribution to row q^s as c_s = (A[q^s][q] + G[q^s][q] x_q) x_q (slot
 // s); two DPP butterflies (partner q^2, then q^1) leave row q's sum in lane q.
+// The compiler contracts c1's product into its sum here and in row_margin; the
+// set-point sweep (rg_lq4_sweep.hip) rounds alike, which a test compares.
 __device__ __forceinline__ float quad_deriv(const QuadLane& L, float s, float x) {
   const float c2 = __builtin_fmaf(L.g2, x, L.a2) * x;
   const float c3 = __builtin_fmaf(L.g3, x, L.a3) * x;
@@ -693,7 +695,9 @@ __global__ void __launch_bounds__(256) k_rollout_lq4_quad(const RollArgs<1, floa
       xs = __builtin_fmaf(h, k3, x);
       const float k4 = quad_deriv(L, s, xs);
       x = __builtin_fmaf(h6, acc + k4, x);
-      if (INJ == 1) x = x + (e0 * w0 + e1 * w1);
+      // one contraction in every copy of the step (left to the compiler, the copies of
+      // the unrolled groups differed, and with them streamed and regenerated draws)
+      if (INJ == 1) x = x + __builtin_fmaf(e0, w0, e1 * w1);
       if (CKPT && ck && --ck_left == 0) {
         ck_left = a.Kc;
         ++ck_seg;

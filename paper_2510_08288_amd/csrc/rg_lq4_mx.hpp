@@ -223,7 +223,7 @@ hipError_t launch_rollout_lq4_mx(const Problem& pr, double band, int early_exit,
                                  int gen_rows, float* gen_w, float* gen_th);
 
 // FP32 set-point sweeps (full horizon, per-scenario margins recorded): how many
-// candidates per lane the one-lane matrix layout takes for M candidates, 0 where
+// candidates per lane the one-lane layout takes for M candidates, 0 where
 // the quad layout is faster.
 int sweep_candidates_per_lane(const Problem& pr, int M);
 hipError_t launch_sweep_lq4(const Problem& pr, double band, int M, int cpl, const DevBuffers& b,

@@ -1,74 +1,97 @@
-// FP32 set-point sweeps of the 4-state plant (rg_margin) on the matrix cores:
-// v_mfma_f32_4x4x1 multiplies, in sixteen blocks at once, a column of a 4 x 4
-// matrix with one value per lane, and leaves the four rows of lane l's product in
-// lane l's four result registers.  So a lane holds one scenario's whole state, a
-// derivative s + A x + G (x.*x) is four squares and eight such instructions, and
-// the one register of matrix columns (A, G, -(F C), E: block b of the register
-// holds column b) serves every lane through the instruction's block broadcast.
-// Each product is one fused multiply-add, added in the order of the other FP32
-// rollouts of this plant.
+// FP32 set-point sweeps of the 4-state plant (rg_margin), one scenario per lane:
+// the whole state in a lane's registers, no exchange between lanes, and draws
+// that are loaded or regenerated once for every candidate the lane takes, where
+// the quad layout regenerates them in all four lanes.
+//
+// A margin must not depend on which or how many other candidates are asked for,
+// and the choice between the two layouts does; so every sum here has the order
+// and the contractions of the quad rollout (quad_deriv and row_margin as
+// compiled, the pairs its two butterflies form), and margins and minimising steps
+// equal it bit for bit.
 #include <hip/hip_runtime.h>
 
 #include "rg_lq4_mx.hpp"
 
 namespace rg {
 
-typedef float f4 __attribute__((ext_vector_type(4)));
+// The model in vector registers, entry [r][s] the one of row r and column r ^ s
+// (a scalar operand makes an FP32 instruction half as long again as a vector
+// one, and two of them do not fit into one instruction).
+struct SweepCoef {
+  float a[4][4], g[4][4], d[4][4], e[4][2], grow[4];
+  float b[4];
+};
 
-// c + column `col` of the matrices times b.
-template <int COL>
-__device__ __forceinline__ f4 mf_col(float m, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_4x4x1f32(m, b, c, 4, COL, 0);
+static SweepCoef make_sweep_coef(const Problem& pr) {
+  const MxCoef m = make_mx_coef(pr);
+  SweepCoef c;
+  for (int r = 0; r < 4; ++r) {
+    for (int s = 0; s < 4; ++s) {
+      c.a[r][s] = (float)m.a[4 * r + (r ^ s)];
+      c.g[r][s] = (float)m.g[4 * r + (r ^ s)];
+      c.d[r][s] = (float)m.d[4 * r + (r ^ s)];
+    }
+    c.e[r][0] = (float)m.e[2 * r];
+    c.e[r][1] = (float)m.e[2 * r + 1];
+    c.b[r] = (float)m.b[r];
+    c.grow[r] = (float)m.grow[r];
+  }
+  return c;
 }
-// out[c] += the four columns from COL0 times x[c], for every candidate c: column
-// by column, so that dependent instructions are CPL apart.
-template <int CPL, int COL0, int Q = 0>
-__device__ __forceinline__ void mf_mat(float m, const f4 (&x)[CPL], f4 (&out)[CPL]) {
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) out[c] = mf_col<COL0 + Q>(m, x[c][Q], out[c]);
-  if constexpr (Q < 3) mf_mat<CPL, COL0, Q + 1>(m, x, out);
+
+// A lane value equal to a uniform one (an identity DPP move).
+__device__ __forceinline__ float lane_value(float x) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xE4, 0xf, 0xf, true));
 }
+__device__ __forceinline__ float sweep_min2(float a, float b) { return b < a ? b : a; }
 
 // Full-horizon rollouts of CPL candidates per lane (blockIdx.y: candidates CPL
-// blockIdx.y ..), one wave per workgroup: the candidates share their scenario's
-// draws, and their independent chains fill the matrix instructions' latency.
-// Bound by issue (FP32 matrix instructions, 2.5 vector slots each, share the
-// pipe with the vector ALU): 38 of them and about 50 vector instructions per
-// candidate-step of 64 scenarios, 265 ns with the SIMDs full, where the quad
-// layout takes 4 x 104 ns and regenerates the draws in every lane of a quad.
-// 17 candidates at N = 16384 H = 1500: 2.65 -> 2.00 ms with streamed draws, 4.48
-// -> 2.82 with regenerated ones; 33 at N = 65536 H = 500: 6.7 -> 4.2, 10.7 -> 4.6.
+// blockIdx.y ..), one wave per workgroup.  Bound by vector issue: about 230
+// instructions per candidate-step of 64 scenarios, 250 ns with the SIMDs full
+// (regenerated draws 290, 260 with three candidates sharing them), where the quad
+// layout takes 4 x 98 ns (4 x 160).  Calls: 17 candidates at N = 16384 H = 1500 2.61
+// -> 1.98 ms with streamed draws, 4.23 -> 2.22 with regenerated ones; 33 at N =
+// 65536 H = 500 6.52 -> 4.23, 10.7 -> 4.32.  (FP32 matrix instructions take 265 and
+// 325 ns, and add in an order of their own.)
 template <int RNG, int INJ, int CPL>
-__global__ void __launch_bounds__(64, 2) k_sweep_lq4(const RollArgs<1, float> a, const MxCoef mc) {
+__global__ void __launch_bounds__(64, 2) k_sweep_lq4(const RollArgs<1, float> a,
+                                                     const SweepCoef sc) {
+#pragma clang fp contract(off)
   constexpr int U = 8;  // steps per group of prefetched draws
   __shared__ unsigned long long sh[16];
   DevSearch* S = a.srch;
   const int c0 = (int)blockIdx.y * CPL;
   if (S->done || c0 >= S->n_cand) return;
-  const int l = threadIdx.x, blk = l >> 2, i4 = l & 3;
+  const int l = threadIdx.x;
   const int k = (int)blockIdx.x * 64 + l;
   const bool live = k < a.N;
   const int kk = live ? k : a.N - 1;  // lanes past N repeat the last scenario
   const uint32_t t = a.st->t;
-  // this lane's element of the matrix columns
-  const float m = (float)(blk < 4    ? mc.a[4 * i4 + blk]
-                          : blk < 8  ? mc.g[4 * i4 + blk - 4]
-                          : blk < 12 ? mc.d[4 * i4 + blk - 8]
-                          : blk < 14 ? mc.e[2 * i4 + blk - 12]
-                                     : 0.0);
-  f4 x[CPL], bv[CPL], grow;
-  float best[CPL];
+  float A[4][4], G[4][4], D[4][4], E[4][2], grow[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      A[r][s] = lane_value(sc.a[r][s]);
+      G[r][s] = lane_value(sc.g[r][s]);
+      D[r][s] = lane_value(sc.d[r][s]);
+    }
+    E[r][0] = lane_value(sc.e[r][0]);
+    E[r][1] = lane_value(sc.e[r][1]);
+    grow[r] = lane_value(sc.grow[r]);
+  }
+  float x[CPL][4], bv[CPL][4], best[CPL];
   int jb[CPL];
+  // smallest row margin, by the quad's lane 0
+  auto row_min = [&](const float* y) {
+#pragma clang fp contract(off)
+    float m[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) grow[r] = (float)mc.grow[r];
-  float mr[CPL];
-  auto row_min = [&]() {
-    f4 y[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) y[c] = grow;
-    mf_mat<CPL, 8>(m, x, y);
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) mr[c] = fminf(fminf(y[c][0], y[c][1]), fminf(y[c][2], y[c][3]));
+    for (int r = 0; r < 4; ++r)
+      m[r] = (__builtin_fmaf(D[r][0], y[r], grow[r]) + D[r][2] * y[r ^ 2]) +
+             __builtin_fmaf(D[r][1], y[r ^ 1], D[r][3] * y[r ^ 3]);
+    return sweep_min2(sweep_min2(m[0], m[1]), sweep_min2(m[2], m[3]));
   };
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
@@ -76,63 +99,58 @@ __global__ void __launch_bounds__(64, 2) k_sweep_lq4(const RollArgs<1, float> a,
     const float v = (float)S->v[cc];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      bv[c][r] = (float)mc.b[r] * v;
+      bv[c][r] = sc.b[r] * v;
       x[c][r] = (float)a.st->x[r];
     }
+    best[c] = row_min(x[c]);
     jb[c] = 0;
   }
-  row_min();
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) best[c] = mr[c];
   const float h = a.h, hh = a.hh, h6 = a.h6;
-  f4 s[CPL], kd[CPL], acc[CPL], xs[CPL];
-  // kd = s + A y + G (y.*y)
-  auto deriv = [&](const f4(&y)[CPL]) {
-    f4 q[CPL];
+  // o = s + A y + G (y.*y)
+  auto deriv = [&](const float* s, const float* y, float* o) {
+#pragma clang fp contract(off)
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      kd[c] = s[c];
-      q[c] = y[c] * y[c];
+    for (int r = 0; r < 4; ++r) {
+      const float c0r = __builtin_fmaf(__builtin_fmaf(G[r][0], y[r], A[r][0]), y[r], s[r]);
+      const float c2r = __builtin_fmaf(G[r][2], y[r ^ 2], A[r][2]) * y[r ^ 2];
+      const float c3r = __builtin_fmaf(G[r][3], y[r ^ 3], A[r][3]) * y[r ^ 3];
+      const float c1r = __builtin_fmaf(__builtin_fmaf(G[r][1], y[r ^ 1], A[r][1]), y[r ^ 1], c3r);
+      o[r] = (c0r + c2r) + c1r;
     }
-    mf_mat<CPL, 0>(m, y, kd);
-    mf_mat<CPL, 4>(m, q, kd);
-  };
-  auto axpy = [](float w, f4 p, f4 q) {
-    f4 o;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) o[r] = __builtin_fmaf(w, p[r], q[r]);
-    return o;
   };
   auto step = [&](float w0, float w1, int jnext) {
-    f4 post = {0.f, 0.f, 0.f, 0.f};
-    if (INJ == 1) post = mf_col<13>(m, w1, mf_col<12>(m, w0, post));
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) s[c] = INJ == 0 ? mf_col<12>(m, w0, bv[c]) : bv[c];
-    if (INJ == 0)
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) s[c] = mf_col<13>(m, w1, s[c]);
-    deriv(x);
-#pragma unroll
-    for (int g = 0; g < 3; ++g) {
-#pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        acc[c] = g == 0 ? kd[c] : axpy(2.f, kd[c], acc[c]);
-        xs[c] = axpy(g < 2 ? hh : h, kd[c], x[c]);
-      }
-      deriv(xs);
-    }
+#pragma clang fp contract(off)
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
-      x[c] = axpy(h6, acc[c] + kd[c], x[c]);
-      if (INJ == 1) x[c] = x[c] + post;
-    }
-    row_min();
+      float s[4], kd[4], acc[4], xs[4];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c)
-      if (mr[c] < best[c]) {
-        best[c] = mr[c];
+      for (int r = 0; r < 4; ++r)
+        s[r] = INJ == 0 ? __builtin_fmaf(E[r][1], w1, __builtin_fmaf(E[r][0], w0, bv[c][r]))
+                        : bv[c][r];
+      deriv(s, x[c], acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) xs[r] = __builtin_fmaf(hh, acc[r], x[c][r]);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        deriv(s, xs, kd);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          acc[r] = __builtin_fmaf(2.f, kd[r], acc[r]);
+          xs[r] = __builtin_fmaf(g == 0 ? hh : h, kd[r], x[c][r]);
+        }
+      }
+      deriv(s, xs, kd);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        x[c][r] = __builtin_fmaf(h6, acc[r] + kd[r], x[c][r]);
+        if (INJ == 1) x[c][r] = x[c][r] + __builtin_fmaf(E[r][0], w0, E[r][1] * w1);
+      }
+      const float m = row_min(x[c]);
+      if (m < best[c]) {
+        best[c] = m;
         jb[c] = jnext;
       }
+    }
   };
   // draws, a group of U steps ahead: buffer loads based at the group's first row
   // (rows past the horizon read as zero)
@@ -185,9 +203,11 @@ __global__ void __launch_bounds__(64, 2) k_sweep_lq4(const RollArgs<1, float> a,
   for (int c = 0; c < CPL; ++c) {
     const int cc = c0 + c;
     if (cc >= S->n_cand) break;  // uniform
-    const f4 d = x[c] - x[c];
+    float bad = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bad += x[c][r] - x[c][r];
     float b = best[c];
-    if (!((d[0] + d[1]) + (d[2] + d[3]) == 0.f) || b != b) b = -INFINITY;
+    if (!(bad == 0.f) || b != b) b = -INFINITY;
     if (live) {
       a.per_m[(size_t)cc * a.N + k] = b;
       a.per_j[(size_t)cc * a.N + k] = jb[c];
@@ -210,28 +230,26 @@ __global__ void __launch_bounds__(64, 2) k_sweep_lq4(const RollArgs<1, float> a,
   }
 }
 
-// Nanoseconds per step of the busiest SIMD, by layout: a wave alone on its SIMD
-// pays its chain's latency, several share the issue slots.  Measured on sweeps of
-// 5 to 33 candidates at N = 1000 .. 65536 (within 10 %): c candidates per lane,
-// streamed / regenerated draws, alone 470 / 555 (c = 1), 770 / 900 (2), 1080 /
-// 1250 (3), else 265 / 380, 560 / 690, 830 / 970 per wave; the quad layout 185 /
-// 290 alone, 104 / 176 per wave of 16 scenarios.
+// Nanoseconds per step of a launch by layout, from the waves of the busiest SIMD:
+// one wave alone pays its chain's latency, several share the issue slots.  Fitted
+// to sweeps of 3 to 33 candidates at N = 1000 .. 65536 (mostly within 10 %),
+// streamed / regenerated draws; two candidates per lane lie between one and three.
 static double sweep_cost(int M, int N, int rng, int c) {
   const long long waves = (long long)div_up((size_t)M, (size_t)c) * div_up((size_t)N, 64);
   const double n = (double)((waves + 1023) / 1024);
-  if (n == 1) return 155.0 + 310.0 * c + (rng ? 50.0 + 40.0 * c : 0.0);
-  return n * (10.0 + 265.0 * c + (rng ? 105.0 + 10.0 * c : 0.0));
+  if (c == 1) return n == 1 ? (rng ? 545.0 : 480.0) : (rng ? 50.0 + 292.0 * n : 45.0 + 250.0 * n);
+  if (n <= 2) return n == 1 ? (rng ? 1315.0 : 1240.0) : (rng ? 1450.0 : 1330.0);
+  return n * (rng ? 790.0 : 770.0);
 }
 static double quad_cost(int M, int N, int rng) {
   const double n = (double)(((long long)M * div_up((size_t)N, 16) + 1023) / 1024);
-  const double alone = rng ? 290.0 : 185.0, t = n * (rng ? 176.0 : 104.0);
-  return t > alone ? t : alone;
+  return rng ? 105.0 + 160.0 * n : 85.0 + 97.5 * n;
 }
 
 int sweep_candidates_per_lane(const Problem& pr, int M) {
   int best = 0;
   double cost = quad_cost(M, pr.s.N, pr.s.rng_mode);
-  for (int c = 1; c <= 3; ++c) {
+  for (int c = 1; c <= 3; c += 2) {
     const double t = sweep_cost(M, pr.s.N, pr.s.rng_mode, c);
     if (t < cost) {
       cost = t;
@@ -244,16 +262,15 @@ int sweep_candidates_per_lane(const Problem& pr, int M) {
 hipError_t launch_sweep_lq4(const Problem& pr, double band, int M, int cpl, const DevBuffers& b,
                             hipStream_t st) {
   const dim3 grid(div_up((size_t)pr.s.N, 64), div_up((size_t)M, (size_t)cpl));
-  const MxCoef mc = make_mx_coef(pr);
+  const SweepCoef sc = make_sweep_coef(pr);
   auto a = make_args<1, float>(pr, band, 0, 1, b);
   return by_bit(pr.s.rng_mode, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
     return by_bit(pr.s.inject, [&](auto ic) {
       constexpr int I = decltype(ic)::value;
       switch (cpl) {
-        case 1: hipLaunchKernelGGL((k_sweep_lq4<R, I, 1>), grid, dim3(64), 0, st, a, mc); break;
-        case 2: hipLaunchKernelGGL((k_sweep_lq4<R, I, 2>), grid, dim3(64), 0, st, a, mc); break;
-        case 3: hipLaunchKernelGGL((k_sweep_lq4<R, I, 3>), grid, dim3(64), 0, st, a, mc); break;
+        case 1: hipLaunchKernelGGL((k_sweep_lq4<R, I, 1>), grid, dim3(64), 0, st, a, sc); break;
+        case 3: hipLaunchKernelGGL((k_sweep_lq4<R, I, 3>), grid, dim3(64), 0, st, a, sc); break;
         default: return hipErrorInvalidValue;
       }
       return hipGetLastError();
