@@ -6,6 +6,23 @@
 
 namespace rg {
 
+// A candidate whose margin at the state itself is below -band is refused without
+// simulating it: the outputs there depend on no draw, so every scenario violates.
+// (What a round then costs is its waves' start-up, and there are nine times as
+// many as with one lane per scenario.)
+template <class T>
+__device__ __forceinline__ bool refused_by_state(const RollArgs<2, T>& a, DevSearch* S, int c,
+                                                 int bx) {
+  const double* x = a.st->x;
+  T y[3];
+  y[0] = t_div(a.pc.c_q0 * (T)x[6], t_fma(a.pc.d1, (T)x[8], a.pc.d0));
+  y[1] = (T)x[0];
+  y[2] = (T)x[6];
+  if (!(margin_rows<3>(a.F, a.g, y) < -a.band)) return false;
+  if (bx == 0 && threadIdx.x == 0) raise_dead(&S->dead[c]);
+  return true;
+}
+
 // blockIdx.y = candidate, seven scenarios per wave.  The per-scenario
 // bookkeeping is that of the one-lane kernel, made by the group's first lane;
 // the margins equal that kernel's bit for bit.  CKPT = 1: the checkpoint
@@ -21,12 +38,16 @@ __device__ __forceinline__ void fc9_lanes_block(const RollArgs<2, T>& a, int c, 
   const bool ck = CKPT == 1 && c == (a.ckpt_cand >= 0 ? a.ckpt_cand : S->nk_idx);
   const int early = a.early && !S->full[c];
   if (refused_by_steady_state(early, S, c, bx)) return;
+  if (!CHANCE && early && refused_by_state<T>(a, S, c, bx)) return;
   const GroupLane gl;
   const int wave = threadIdx.x >> 6;
   const int k = (int)(bx * (blockDim.x >> 6) + wave) * kWaveGroups + gl.grp;
   const uint32_t t = a.st->t;
   const int q = CHANCE ? S->q : 0;
-  const bool live = gl.grp < kWaveGroups && k < a.N;
+  // A wave that starts after its candidate died has nothing to decide, and a dead
+  // candidate's margin keys are not read.
+  const bool over = early && __builtin_amdgcn_readfirstlane(is_dead(&S->dead[c]));
+  const bool live = !over && gl.grp < kWaveGroups && k < a.N;
   T m = t_inf<T>();
   int jb = 0, ns = 0;
   if (live) {  // whole groups are active or inactive together
@@ -45,8 +66,7 @@ __device__ __forceinline__ void fc9_lanes_block(const RollArgs<2, T>& a, int c, 
         a.per_j[(size_t)c * a.N + k] = jb;
       }
       if (m < -a.band) {
-        if (q == 0 || atomicAdd(&S->nviol[c], 1) >= q)
-          __hip_atomic_store(&S->dead[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (q == 0 || atomicAdd(&S->nviol[c], 1) >= q) raise_dead(&S->dead[c]);
       } else if (m < a.band && !stopped) {
         const int idx = atomicAdd(&S->n_recheck, 1);
         a.rlist[idx] = make_int2(c, k);
@@ -60,10 +80,13 @@ __device__ __forceinline__ void fc9_lanes_block(const RollArgs<2, T>& a, int c, 
   int wsum = own ? ns : 0;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) wsum += __shfl_xor(wsum, off);
-  if ((threadIdx.x & 63) == 0) atomicAdd(&S->lane_steps, (unsigned long long)wsum);
+  const unsigned long long steps = block_sum_waves((unsigned long long)wsum, sh);
   if (threadIdx.x == 0) {
-    atomicMin(&S->key_all[c], kall);
-    if (kfar != ~0ull) atomicMin(&S->key_far[c], kfar);
+    if (steps) atomicAdd(&S->lane_steps, steps);
+    const bool fell = !CHANCE && early && kall != ~0ull &&
+                      key_margin(kall, sizeof(T) == 8) < -(double)a.band;
+    if (kall != ~0ull && !fell) atomicMin(&S->key_all[c], kall);
+    if (kfar != ~0ull && !fell) atomicMin(&S->key_far[c], kfar);
   }
 }
 

@@ -223,8 +223,7 @@ __device__ __forceinline__ T rollout_fc9_lanes(const RollArgs<2, T>& a, int earl
           // every group of the wave evaluates the same candidate
           const bool viol = best < -a.band;
           if (__builtin_amdgcn_ballot_w64(viol) != 0) {
-            if (viol && i == 0)
-              __hip_atomic_store(stop_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (viol && i == 0) raise_dead(stop_flag);
             *stopped = true;
             run = false;
             break;

@@ -27,7 +27,11 @@ enum Mode { kBisect = 0, kGrid = 1, kNewton = 2 };
 // round reads steps t .. t + kSpecMax, and the draw workgroups of a step's
 // first round may write up to t + kPairs - 1).
 constexpr int kSpecMax = 7;
-constexpr int kMssCache = 64;
+// Steady-state margins kept by set-point: those of the largest round, for a
+// governor that holds v meets the same set-points again, and the tree beside a
+// predicted round alone has up to 63.  The 9-state plant's Newton iterations take
+// 130 us a round whatever their number, the 4-state plant's 9 us.
+constexpr int kMssCache = 128;
 constexpr int kPairs = kSpecMax + 3;
 
 struct DevState {

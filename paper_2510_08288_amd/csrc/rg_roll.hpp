@@ -188,6 +188,29 @@ __device__ __forceinline__ unsigned long long block_min_u64(unsigned long long v
   return v;
 }
 
+// A candidate's dead flag, shared by all its waves: one that is set is not set
+// again.  Stores and atomics on one line take their turn at the memory side,
+// about 20 ns each, and where every scenario violates at once each wave has one.
+__device__ __forceinline__ bool is_dead(const int32_t* flag) {
+  return __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+__device__ __forceinline__ void raise_dead(int32_t* flag) {
+  if (!is_dead(flag)) __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum over a workgroup's waves of a value uniform over each; in thread 0.
+__device__ __forceinline__ unsigned long long block_sum_waves(unsigned long long v,
+                                                               unsigned long long* sh) {
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int nw = (blockDim.x + 63) >> 6;
+    for (int i = 1; i < nw; ++i) v += sh[i];
+  }
+  __syncthreads();
+  return v;
+}
+
 // Step offset of candidate c: 0 for the step's own candidates, j for a
 // speculative candidate of step t + j (closed loop, round 0).
 __device__ __forceinline__ int cand_step(const DevSearch* S, int c) {
