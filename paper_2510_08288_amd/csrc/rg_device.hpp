@@ -120,9 +120,10 @@ __device__ __forceinline__ float t_tanh_m1(float x, float nk) {
   const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(2.8853900817779268f, x, nk));
   return __builtin_amdgcn_rcpf(__builtin_fmaf(-0.5f, e, -0.5f));
 }
-// n / d for d normal and finite and a quotient in the normal range: reciprocal,
-// two Newton steps, and the residual's correction, the sequence of the compiler's
-// division without its scaling of extreme operands.
+// n / d for d normal and finite and a quotient in the normal range, without the
+// scaling of extreme operands: reciprocal refined by Newton steps, quotient, and
+// Markstein's correction by the residual n - d q (P. Markstein, IBM J. Res. Dev.
+// 34, 1990).
 __device__ __forceinline__ double t_div(double n, double d) {
   double r = __builtin_amdgcn_rcp(d);
   r = fma(fma(-d, r, 1.0), r, r);
@@ -134,6 +135,14 @@ __device__ __forceinline__ float t_div(float n, float d) {
   const float r = __builtin_amdgcn_rcpf(d);
   const float q = n * r;
   return __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
+}
+// The same with the special cases of a division (zero, infinite and NaN operands):
+// a plant's output may have a denominator that is zero.
+__device__ __forceinline__ double t_quot(double n, double d) {
+  return __builtin_amdgcn_div_fixup(t_div(n, d), d, n);
+}
+__device__ __forceinline__ float t_quot(float n, float d) {
+  return __builtin_amdgcn_div_fixupf(t_div(n, d), d, n);
 }
 // FP64 tanh of the FP64 rollouts and steady-state solves (written here, not
 // the library's): tanh|z| = t / (t + 2) with t = expm1(2|z|), which has no
@@ -179,8 +188,9 @@ __device__ __forceinline__ double t_tanh(double z) {
 }
 __device__ __forceinline__ float t_sqrt(float z) { return __builtin_amdgcn_sqrtf(z); }
 // FP64 square root of z >= 0: reciprocal square root, one coupled Newton step
-// and two residual corrections.  Below 2^-960 (where the compiler's sqrt scales
-// its operand) the result is 0, an absolute error of at most 2^-480.
+// (Goldschmidt's iteration) and two residual corrections.  Zero, infinity and NaN
+// are their own roots; a subnormal z, which the instruction cannot start from,
+// stays as it is, an absolute error below 2^-511.
 __device__ __forceinline__ double t_sqrt(double z) {
   const double y = __builtin_amdgcn_rsq(z);
   double g = z * y, h = 0.5 * y;
@@ -189,7 +199,7 @@ __device__ __forceinline__ double t_sqrt(double z) {
   h = fma(h, r, h);
   g = fma(fma(-g, g, z), h, g);
   g = fma(fma(-g, g, z), h, g);
-  return z < 0x1p-960 ? 0.0 : g;
+  return __builtin_amdgcn_class(z, 0x100) ? g : z;  // positive normal
 }
 __device__ __forceinline__ float t_min(float a, float b) { return fminf(a, b); }
 __device__ __forceinline__ double t_min(double a, double b) { return fmin(a, b); }
@@ -448,7 +458,7 @@ struct Plant<2, T> {
     for (int i = 0; i < 9; ++i) x[i] = x[i] + w[i];
   }
   __device__ static void output(const Coef& c, const Lane&, const T* x, T* y) {
-    y[0] = t_div(c.c_q0 * x[6], t_fma(c.d1, x[8], c.d0));
+    y[0] = t_quot(c.c_q0 * x[6], t_fma(c.d1, x[8], c.d0));
     y[1] = x[0];
     y[2] = x[6];
   }

@@ -15,7 +15,7 @@ __device__ __forceinline__ bool refused_by_state(const RollArgs<2, T>& a, DevSea
                                                  int bx) {
   const double* x = a.st->x;
   T y[3];
-  y[0] = t_div(a.pc.c_q0 * (T)x[6], t_fma(a.pc.d1, (T)x[8], a.pc.d0));
+  y[0] = t_quot(a.pc.c_q0 * (T)x[6], t_fma(a.pc.d1, (T)x[8], a.pc.d0));
   y[1] = (T)x[0];
   y[2] = (T)x[6];
   if (!(margin_rows<3>(a.F, a.g, y) < -a.band)) return false;

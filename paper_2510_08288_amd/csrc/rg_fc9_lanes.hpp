@@ -144,7 +144,7 @@ __device__ __forceinline__ T rollout_fc9_lanes(const RollArgs<2, T>& a, int earl
   };
   auto margin = [&]() -> T {
     T y[P::ny];
-    y[0] = t_div(a.pc.c_q0 * X6, t_fma(a.pc.d1, slot[kX + 2], a.pc.d0));
+    y[0] = t_quot(a.pc.c_q0 * X6, t_fma(a.pc.d1, slot[kX + 2], a.pc.d0));
     y[1] = X0;
     y[2] = X6;
     const T m = margin_rows<P::ny>(a.F, a.g, y);
