@@ -754,11 +754,22 @@ __device__ __forceinline__ T margin_rows_arg(const T* F, const T* g, const T* y,
   return best;
 }
 
-// NaN if any row is NaN (the caller maps it to -inf): the minimum ignores NaN
-// rows, and the sum of the rows is NaN exactly when one of them is, or when one
-// is -inf beside a +inf padding row.
+// Margin over the rows, NaN if any row is NaN (the caller maps it to -inf).  With
+// two outputs (the 4-state plant's one-lane rollouts) each row is g - F y, taken in
+// turn.  With three, rows are chains of fma and the minimum ignores NaN rows: the
+// sum of the rows is NaN exactly when one of them is, or when one is -inf beside a
+// +inf padding row.
 template <int NY, class T>
 __device__ __forceinline__ T margin_rows(const T* F, const T* g, const T* y) {
+  if constexpr (NY == 2) {
+    T best = t_inf<T>();
+#pragma unroll
+    for (int r = 0; r < kNC; ++r) {
+      const T m = g[r] - t_fma(F[r * NY + 1], y[1], F[r * NY] * y[0]);
+      best = (m < best || m != m) ? m : best;
+    }
+    return best;
+  }
   static_assert(kNC == 4, "four rows");
   T m[kNC];
 #pragma unroll
