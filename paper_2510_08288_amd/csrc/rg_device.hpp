@@ -157,9 +157,11 @@ __device__ __forceinline__ float t_quot(float n, float d) {
 // Branch-free: arguments at or beyond 40 run the same arithmetic on 40, where
 // the quotient rounds to 1; NaN stays NaN.  Within 3 ulp of tanh over the arguments the
 // rollouts meet (checked against an extended-precision reference in the tests).
+// IEEE: the quotient by the compiler's division (the steady-state solves, eq_deriv).
+template <bool IEEE = false>
 __device__ __forceinline__ double t_tanh(double z) {
   const double ax = 2.0 * fabs(z);
-  const double x = ax > 40.0 ? 40.0 : ax;
+  const double x = IEEE ? fmin(ax, 40.0) : (ax > 40.0 ? 40.0 : ax);
   constexpr double kLn2Head = 0x1.62e42ff0p-1;         // ln 2 to 32 significant bits
   constexpr double kLn2Tail = -0x1.718432a1b0e26p-35;  // ln 2 - kLn2Head
   constexpr double kInvLn2 = 0x1.71547652b82fep+0;
@@ -184,6 +186,11 @@ __device__ __forceinline__ double t_tanh(double z) {
   const double em = p * r;  // expm1(r)
   const double two_k = ldexp(1.0, (int)k);
   const double t = fma(two_k, em, two_k - 1.0);
+  if constexpr (IEEE) {
+    const double th = copysign(t / (t + 2.0), z);
+    const double sat = ax == ax ? copysign(1.0, z) : z;
+    return ax < 40.0 ? th : sat;
+  }
   return copysign(t_div(t, t + 2.0), z);
 }
 __device__ __forceinline__ float t_sqrt(float z) { return __builtin_amdgcn_sqrtf(z); }
@@ -258,6 +265,9 @@ struct Plant<1, T> {
       for (int j = 0; j < 4; ++j) a = t_fma(c.G[4 * i + j], q[j], a);
       xd[i] = a;
     }
+  }
+  __device__ static void eq_deriv(const Coef& c, const Lane& L, const T* s, const T* x, T* xd) {
+    deriv(c, L, s, x, xd);
   }
   __device__ static void post(const Coef& c, const T* w, T* x) {
 #pragma unroll
@@ -409,9 +419,10 @@ struct Plant<2, T> {
   }
   // What the coupling matrix multiplies: FP32 tanh - 1 (its row sums are in the
   // step forcing), FP64 tanh.
+  template <bool IEEE = false>
   __device__ static T act(T x, T xbar, T nkxbar) {
     if constexpr (sizeof(T) == 4) return t_tanh_m1(x, nkxbar);
-    else return t_tanh(x - xbar);
+    else return t_tanh<IEEE>(x - xbar);
   }
   // Row i of the derivative: s_i - K R - A x_i + W_i . act + P Q, one fma per
   // term in this order, nothing contracted, so that the one-lane derivative and
@@ -428,17 +439,20 @@ struct Plant<2, T> {
   }
   // Square-root factor of the orifice flow q_{l+1}: sqrt(max(p_l - p_{l+1}, 0))
   // with p_7 = p_amb.
+  template <bool IEEE = false>
   __device__ static T orifice(T pl, T pn) {
-    const T dp = pl - pn;
-    return t_sqrt(dp > (T)0 ? dp : (T)0);
+    const T dp = pl - pn, z = dp > (T)0 ? dp : (T)0;
+    if constexpr (IEEE) return sqrt(z);
+    else return t_sqrt(z);
   }
+  template <bool IEEE = false>
   __device__ static void deriv(const Coef& c, const Lane& L, const T* s, const T* x, T* xd) {
 #pragma clang fp contract(off)
     T tz[9], r[6];
 #pragma unroll
-    for (int j = 0; j < 9; ++j) tz[j] = act(x[j], c.xbar[j], c.nkxbar[j]);
+    for (int j = 0; j < 9; ++j) tz[j] = act<IEEE>(x[j], c.xbar[j], c.nkxbar[j]);
 #pragma unroll
-    for (int l = 0; l < 6; ++l) r[l] = orifice(x[l], (l < 5) ? x[l + 1] : c.p_amb);
+    for (int l = 0; l < 6; ++l) r[l] = orifice<IEEE>(x[l], (l < 5) ? x[l + 1] : c.p_amb);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       T a = s[i];
@@ -452,6 +466,13 @@ struct Plant<2, T> {
       else if (i == 7) a = t_fma(L.b2v, x[6], a);
       xd[i] = a;
     }
+  }
+  // The derivative the steady-state solves iterate on.  With the rollouts' quotient
+  // and square root, and with either of them, its kernels come out a seventh slower
+  // (4096 solves 218 us against 189): the solve is bound by the order the compiler
+  // finds for one lane's chain, not by these sequences' length.
+  __device__ static void eq_deriv(const Coef& c, const Lane& L, const T* s, const T* x, T* xd) {
+    deriv<true>(c, L, s, x, xd);
   }
   __device__ static void post(const Coef&, const T* w, T* x) {
 #pragma unroll
@@ -577,7 +598,7 @@ struct Plant<2, T> {
     const T* b = c.thnom + 15;
     const T* mu = c.thnom + 18;
     for (int j = 0; j < 9; ++j) {
-      const T tj = t_tanh(x[j] - c.xbar[j]);
+      const T tj = t_tanh<true>(x[j] - c.xbar[j]);
       const T dj = 1 - tj * tj;
       for (int i = 0; i < 9; ++i) J[9 * i + j] = c.W[9 * i + j] * dj;
     }
@@ -586,7 +607,7 @@ struct Plant<2, T> {
     for (int l = 0; l < 6; ++l) {
       const T dn = (l < 5) ? x[l + 1] : c.p_amb;
       const T dp = x[l] - dn;
-      const T d = dp > 0 ? kq[l] / (2 * t_sqrt(dp)) : (T)0;  // dq_{l+1}/dp_l
+      const T d = dp > 0 ? kq[l] / (2 * sqrt(dp)) : (T)0;  // dq_{l+1}/dp_l
       J[9 * l + l] -= d;
       if (l < 5) {
         J[9 * l + l + 1] += d;

@@ -1065,7 +1065,7 @@ __device__ double steady_margin(const typename Plant<KIND, double>::Coef& pc, co
   P::force0(pc, L, s0);
   bool ok = false;
   for (int it = 0; it <= 50; ++it) {
-    P::deriv(pc, L, s0, x, f);
+    P::eq_deriv(pc, L, s0, x, f);
     double nrm = 0.0;
     for (int i = 0; i < P::n; ++i) {
       if (!isfinite(f[i])) return -INFINITY;
@@ -2566,7 +2566,7 @@ __device__ double steady_grad(const typename Plant<KIND, double>::Coef& pc, cons
   P::force0(pc, L, s0);
   bool ok = false;
   for (int it = 0; it <= 50; ++it) {
-    P::deriv(pc, L, s0, x, f);
+    P::eq_deriv(pc, L, s0, x, f);
     double nrm = 0.0;
     for (int i = 0; i < n; ++i) nrm = fmax(nrm, fabs(f[i]));
     if (!(nrm == nrm)) return -INFINITY;
@@ -2732,7 +2732,7 @@ __global__ void k_equilibrium(const CtlArgs<KIND> a, double v, double* out) {
   P::force0(a.pc, L, s0);
   bool conv = false;
   for (int it = 0; ok && it <= 50; ++it) {
-    P::deriv(a.pc, L, s0, x, f);
+    P::eq_deriv(a.pc, L, s0, x, f);
     double nrm = 0.0;
     for (int i = 0; i < n; ++i) nrm = fmax(nrm, fabs(f[i]));
     if (!(nrm == nrm)) break;
