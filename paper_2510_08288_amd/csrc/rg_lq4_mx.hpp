@@ -183,8 +183,9 @@ __device__ __forceinline__ int mx_rollout(const MxLane<RNG, INJ>& M, const RollA
     M.step(w, u, x);
     const double m = M.margin(x);
     if (RECORD) {
-      if (m < bm) {
-        bm = m;
+      const double mm = m == m ? m : -INFINITY;  // a state that left the range
+      if (mm < bm) {
+        bm = mm;
         jq = j + 1;
       }
     } else {
