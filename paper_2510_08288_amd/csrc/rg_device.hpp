@@ -157,7 +157,7 @@ __device__ __forceinline__ float t_quot(float n, float d) {
 // Branch-free: arguments at or beyond 40 run the same arithmetic on 40, where
 // the quotient rounds to 1; NaN stays NaN.  Within 3 ulp of tanh over the arguments the
 // rollouts meet (checked against an extended-precision reference in the tests).
-// IEEE: the quotient by the compiler's division (the steady-state solves, eq_deriv).
+// IEEE: the quotient by the compiler's division (eq_deriv).
 template <bool IEEE = false>
 __device__ __forceinline__ double t_tanh(double z) {
   const double ax = 2.0 * fabs(z);
@@ -266,6 +266,7 @@ struct Plant<1, T> {
       xd[i] = a;
     }
   }
+  template <bool IEEE>
   __device__ static void eq_deriv(const Coef& c, const Lane& L, const T* s, const T* x, T* xd) {
     deriv(c, L, s, x, xd);
   }
@@ -334,6 +335,7 @@ struct Plant<1, T> {
 #pragma unroll
     for (int i = 0; i < 4; ++i) fv[i] = c.B[i];
   }
+  template <bool IEEE = false>
   __device__ static void jacobian(const Coef& c, const T* x, T, T* J) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -467,12 +469,15 @@ struct Plant<2, T> {
       xd[i] = a;
     }
   }
-  // The derivative the steady-state solves iterate on.  With the rollouts' quotient
-  // and square root, and with either of them, its kernels come out a seventh slower
-  // (4096 solves 218 us against 189): the solve is bound by the order the compiler
-  // finds for one lane's chain, not by these sequences' length.
+  // The derivative the steady-state solves iterate on.  IEEE (Alg. 2's table of
+  // them): with the rollouts' quotient and square root that kernel comes out a
+  // seventh slower (4096 solves 218 us against 189), while the solves inside the
+  // batches' kernels are faster with them (a small batch's step 0.47 ms against
+  // 0.69): bound by the order the compiler finds for one lane's chain, not by these
+  // sequences' length.
+  template <bool IEEE>
   __device__ static void eq_deriv(const Coef& c, const Lane& L, const T* s, const T* x, T* xd) {
-    deriv<true>(c, L, s, x, xd);
+    deriv<IEEE>(c, L, s, x, xd);
   }
   __device__ static void post(const Coef&, const T* w, T* x) {
 #pragma unroll
@@ -592,13 +597,14 @@ struct Plant<2, T> {
   }
   __device__ static bool eq_guess_needs_solve() { return false; }
   // df/dx at nominal theta, w = 0.
+  template <bool IEEE = false>
   __device__ static void jacobian(const Coef& c, const T* x, T v, T* J) {
     const T* a = c.thnom;
     const T* kq = c.thnom + 9;
     const T* b = c.thnom + 15;
     const T* mu = c.thnom + 18;
     for (int j = 0; j < 9; ++j) {
-      const T tj = t_tanh<true>(x[j] - c.xbar[j]);
+      const T tj = t_tanh<IEEE>(x[j] - c.xbar[j]);
       const T dj = 1 - tj * tj;
       for (int i = 0; i < 9; ++i) J[9 * i + j] = c.W[9 * i + j] * dj;
     }
@@ -607,7 +613,7 @@ struct Plant<2, T> {
     for (int l = 0; l < 6; ++l) {
       const T dn = (l < 5) ? x[l + 1] : c.p_amb;
       const T dp = x[l] - dn;
-      const T d = dp > 0 ? kq[l] / (2 * sqrt(dp)) : (T)0;  // dq_{l+1}/dp_l
+      const T d = dp > 0 ? kq[l] / (2 * (IEEE ? sqrt(dp) : t_sqrt(dp))) : (T)0;  // dq_{l+1}/dp_l
       J[9 * l + l] -= d;
       if (l < 5) {
         J[9 * l + l + 1] += d;

@@ -1050,7 +1050,7 @@ __device__ bool dense_solve(double* J, double* b) {
 // Tightened steady-state margin min_r (g_r - eps |g_r| - F_r y_ss(v)) with the
 // equilibrium from Newton's method (nominal coefficients, w = 0); failure to
 // reach ||f||_inf <= 1e-12 within 50 iterations gives -inf.
-template <int KIND>
+template <int KIND, bool IEEE = false>
 __device__ double steady_margin(const typename Plant<KIND, double>::Coef& pc, const DevSearch* S,
                                 double v) {
   using P = Plant<KIND, double>;
@@ -1065,7 +1065,7 @@ __device__ double steady_margin(const typename Plant<KIND, double>::Coef& pc, co
   P::force0(pc, L, s0);
   bool ok = false;
   for (int it = 0; it <= 50; ++it) {
-    P::eq_deriv(pc, L, s0, x, f);
+    P::template eq_deriv<IEEE>(pc, L, s0, x, f);
     double nrm = 0.0;
     for (int i = 0; i < P::n; ++i) {
       if (!isfinite(f[i])) return -INFINITY;
@@ -1076,7 +1076,7 @@ __device__ double steady_margin(const typename Plant<KIND, double>::Coef& pc, co
       break;
     }
     if (it == 50) break;
-    P::jacobian(pc, x, v, J);
+    P::template jacobian<IEEE>(pc, x, v, J);
     for (int i = 0; i < P::n; ++i) f[i] = -f[i];
     if (!dense_solve<P::n>(J, f)) return -INFINITY;
     for (int i = 0; i < P::n; ++i) x[i] += f[i];
@@ -2034,7 +2034,7 @@ __global__ void __launch_bounds__(64) k_alg2_setup(const CtlArgs<KIND> ctl, doub
   }
   if (i < nodes) {
     const double v = cand_v(alg2_node_kappa(i), ctl.st->r, ctl.st->v_prev);
-    mss_tab[i] = steady_margin<KIND>(ctl.pc, S, v);
+    mss_tab[i] = steady_margin<KIND, true>(ctl.pc, S, v);
   }
 }
 
@@ -2566,7 +2566,7 @@ __device__ double steady_grad(const typename Plant<KIND, double>::Coef& pc, cons
   P::force0(pc, L, s0);
   bool ok = false;
   for (int it = 0; it <= 50; ++it) {
-    P::eq_deriv(pc, L, s0, x, f);
+    P::deriv(pc, L, s0, x, f);
     double nrm = 0.0;
     for (int i = 0; i < n; ++i) nrm = fmax(nrm, fabs(f[i]));
     if (!(nrm == nrm)) return -INFINITY;
@@ -2732,7 +2732,7 @@ __global__ void k_equilibrium(const CtlArgs<KIND> a, double v, double* out) {
   P::force0(a.pc, L, s0);
   bool conv = false;
   for (int it = 0; ok && it <= 50; ++it) {
-    P::eq_deriv(a.pc, L, s0, x, f);
+    P::deriv(a.pc, L, s0, x, f);
     double nrm = 0.0;
     for (int i = 0; i < n; ++i) nrm = fmax(nrm, fabs(f[i]));
     if (!(nrm == nrm)) break;
