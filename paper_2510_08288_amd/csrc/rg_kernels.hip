@@ -1187,29 +1187,40 @@ template <int KIND>
 __device__ void prepare_candidates(const typename Plant<KIND, double>::Coef& pc, const DevState* st,
                                    DevSearch* S) {
   const double r = st->r, vp = st->v_prev;
-  __shared__ double s_cv[kMssCache], s_cm[kMssCache], s_v[kCMax], s_m[kCMax];
-  __shared__ int s_miss[kCMax];
-  for (int i = threadIdx.x; i < kMssCache; i += blockDim.x) {
-    s_cv[i] = S->mss_v[i];
-    s_cm[i] = S->mss_m[i];
-  }
+  __shared__ double s_v[kCMax], s_m[kCMax];
+  __shared__ int s_hit[kCMax], s_miss[kCMax];
+  const int lane = threadIdx.x & 63;
+  static_assert(kMssCache == 128, "two entries per lane");
+  const double cv0 = S->mss_v[lane], cv1 = S->mss_v[lane + 64];
   const int n = S->n_cand < kCMax ? S->n_cand : kCMax;
   const int next = S->mss_next;
-  __syncthreads();
   for (int c = threadIdx.x; c < n; c += blockDim.x) {
-    if (S->mode != kNewton) S->full[c] = 0;
     // a speculative candidate of step t + j: that step's reference; its v_prev
     // is this step's (holds), or any (kappa = 1 gives v = r)
     const int sj = cand_step(S, c);
     const double v = cand_v(S->kappa[c], sj ? S->r_spec[sj - 1] : r, vp);
     S->v[c] = v;
-    int hit = -1;
-#pragma unroll 8
-    for (int i = 0; i < kMssCache; ++i) hit = s_cv[i] == v ? i : hit;
-    const double m = hit >= 0 ? s_cm[hit] : steady_margin<KIND>(pc, S, v);
+    s_v[c] = v;
+  }
+  __syncthreads();
+  // look-up: a wave holds the whole cache and takes a candidate at a time (a thread
+  // per candidate scanning the entries in LDS took up to 10 us for 128 of them)
+#pragma unroll 4
+  for (int c = threadIdx.x >> 6; c < n; c += (blockDim.x + 63) >> 6) {
+    const double v = s_v[c];
+    const unsigned long long h0 = __builtin_amdgcn_ballot_w64(cv0 == v);
+    const unsigned long long h1 = __builtin_amdgcn_ballot_w64(cv1 == v);
+    if (lane == 0)
+      s_hit[c] = h0 ? __builtin_ctzll(h0) : (h1 ? 64 + __builtin_ctzll(h1) : -1);
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < n; c += blockDim.x) {
+    if (S->mode != kNewton) S->full[c] = 0;
+    const double v = s_v[c];
+    const int hit = s_hit[c];
+    const double m = hit >= 0 ? S->mss_m[hit] : steady_margin<KIND>(pc, S, v);
     S->mss[c] = m;
     s_miss[c] = hit < 0;
-    s_v[c] = v;
     s_m[c] = m;
     S->key_all[c] = ~0ull;
     S->key_far[c] = ~0ull;
