@@ -149,9 +149,10 @@ typedef struct rg_options {
     int32_t K;             /* halvings after the kappa = 1 probe (default 12) */
     int32_t search;        /* enum rg_search (default BISECT) */
     int32_t depth;         /* bisection levels evaluated per device round (1..6; 0 = auto:
-                              from the problem's size, and later rounds may follow the
-                              bisection path to the root predicted from the margins so
-                              far instead; the result is the same) */
+                              from the problem's size).  With predict (grids: a refinement
+                              deeper than one round) later rounds may follow the bisection
+                              path to the root predicted from the margins so far instead;
+                              the result is the same */
     int32_t M;             /* grid points for RG_SEARCH_GRID (2..127) */
     int32_t refine;        /* halvings after the grid */
     int32_t early_exit;    /* 1: a candidate stops once one lane is below -band */
@@ -174,7 +175,7 @@ typedef struct rg_options {
                               1); later rounds use the speculative tree.  Only which
                               candidates are evaluated early changes: the result is that of
                               sequential bisection either way.  0: tree from round 0.
-                              With depth = 0 and few scenarios the predicted round also
+                              With few scenarios the predicted round also
                               evaluates the tree's first levels (a single step's also beside
                               the probe alone), so that a wrong guess costs no round.
                               Newton searches: after a step that held v (kappa = 0), 1 makes
@@ -368,8 +369,8 @@ int rg_get_options(const rg_handle* h, rg_options* out);
  * two counts): lanes per scenario (FP32 rollouts: 1 or 4 for LQ4, 1 or 16 for
  * FC9 with the robust verdict), rollout workgroup (128 or 256 threads), device
  * search depth (2..5; 1..3 for the grid refinement), first-round prediction
- * (on/off, bisection only) and the
- * speculation depth (7, 3, 1, 0; with prediction and 4 lanes).  Schedules
+ * (on/off, bisection only) and the speculation depth (7, 3, 1, 0; with
+ * prediction and 4 lanes), the schedule in force first.  Schedules
  * change only which candidates run when, so every one must give the same kappa
  * sequence; a mismatch returns RG_E_STATE.  best_out (nullable) receives the
  * fastest schedule's options, best_ms_out (nullable) its time per update; with
@@ -440,9 +441,9 @@ int rg_equilibrium(rg_handle* h, double v, double* x_out);
  * flat rollout launch (all their scenario tiles in one grid, FP32, one lane per
  * scenario, or for the longest horizons of the 9-state plant a group of lanes),
  * then their FP64 rechecks and decisions.  All instances
- * use one search depth (opt.depth = 0: from the sum of N over the batch, and
- * rounds along the predicted bisection path; large
- * batches evaluate one candidate per round).  opt: precision F32_RECHECK,
+ * use one search depth (opt.depth = 0: from the sum of N over the batch) and, up
+ * to 2^20 scenarios in all, rounds along the predicted bisection path; large
+ * batches evaluate one candidate per round.  opt: precision F32_RECHECK,
  * search BISECT or GRID, chance_q 0 (else RG_E_NOTSUP); block is the scenario
  * tile (64, 128, 256); predict as for rg_create; persistent_wgs is accepted
  * and unused.  opt = NULL: the defaults of rg_default_options except block =
@@ -467,8 +468,9 @@ int rg_batch_get_options(const rg_batch* b, rg_options* out);
  * rg_batch_create), runs its steps t = 0, 1, 2 from the states x and references r,
  * v_prev (as rg_batch_step, graph replay; the first step allocates and
  * captures) and times the faster of the last two; the batch is then
- * destroyed.  Lanes per scenario are not a choice: batches run one lane per
- * scenario.  Schedules change only which candidates run when, so every one must
+ * destroyed.  Lanes per scenario are not a choice (the batch picks them by
+ * instance); of small batches, whose automatic depth is above 3, time the
+ * defaults too.  Schedules change only which candidates run when, so every one must
  * give the same kappa at every step; a mismatch returns RG_E_STATE.  best_out
  * (nullable) receives the fastest schedule's options (depth resolved),
  * best_ms_out (nullable) its time per batched step in ms.  Errors as

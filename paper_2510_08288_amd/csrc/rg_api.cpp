@@ -24,7 +24,7 @@ struct rg_handle {
   Problem pr;
   rg_options opt;
   LaunchCfg cfg;
-  bool auto_depth = false;  // opt.depth was left to the library
+  bool member = false;      // of a batch
   int pred_tree = 0;        // tree levels of a predicted round 0
   int batch_path = 0;       // batch member: candidates of a round along the predicted path
   int path = 0;             // the same, as planned (0: trees only)
@@ -246,11 +246,10 @@ int depth_for(const rg_handle* h, int lanes) {
 
 // Levels of the bisection tree that a predicted round 0 also evaluates, so that
 // a wrong guess costs no round: as many as keep the whole round (probe, tree,
-// the predicted path below it) within the wave budget; none with a depth the
-// caller chose.
+// the predicted path below it) within the wave budget.
 int pred_tree_for(const rg_handle* h, int lanes) {
   const int K = h->opt.K;
-  if (!h->auto_depth || h->opt.search != RG_SEARCH_BISECT || !h->opt.predict) return 0;
+  if (h->member || h->opt.search != RG_SEARCH_BISECT || !h->opt.predict) return 0;
   const double per_cand = waves_per_candidate(h, lanes), budget = wave_budget(h, lanes);
   int d = 0;
   while (d < 6 && d < K && (1 + ((1 << (d + 1)) - 1) + K - (d + 1)) * per_cand <= budget) ++d;
@@ -288,13 +287,14 @@ void plan(rg_handle* h) {
       c.rounds = 1 + (h->opt.K + d - 1) / d;
     }
   }
-  // Rounds along the predicted path (decide_body), where the depth is the
-  // library's: as many candidates as the workspace holds anyway.  A grid's
-  // refinement takes one more round, so that one guess may be wrong (bisection
-  // has it: round 0 counts no level).
+  // Rounds along the predicted path (decide_body), as many candidates as the
+  // workspace holds anyway.  A grid's refinement takes one more round, so that one
+  // guess may be wrong (bisection has it: round 0 counts no level).  Whether the
+  // depth is the caller's makes no difference: the options in force describe the
+  // whole schedule.
   h->path = h->batch_path;
-  if (h->auto_depth && h->opt.search == RG_SEARCH_BISECT && h->opt.predict) h->path = h->opt.K;
-  if (h->auto_depth && h->opt.search == RG_SEARCH_GRID && h->opt.refine > d) {
+  if (!h->member && h->opt.search == RG_SEARCH_BISECT && h->opt.predict) h->path = h->opt.K;
+  if (!h->member && h->opt.search == RG_SEARCH_GRID && h->opt.refine > d) {
     h->path = std::min(h->opt.refine, c.cmax_round);
     c.rounds += 1;
   }
@@ -823,7 +823,6 @@ int rg_create(const rg_plant* plant, const rg_scenarios* scen, const rg_constrai
   h->pr.H = H;
   h->pr.dt = dt;
   h->opt = o;
-  h->auto_depth = o.depth == 0;
   plan(h);
   *out = h;
   return RG_OK;
@@ -1273,9 +1272,7 @@ int reset_search_schedule(rg_handle* h) {
   return RG_OK;
 }
 
-// auto_depth: o.depth is the library's own choice, not a schedule's.
-int apply_schedule(rg_handle* h, const rg_options& o, bool auto_depth) {
-  h->auto_depth = auto_depth;
+int apply_schedule(rg_handle* h, const rg_options& o) {
   h->opt.lanes = o.lanes;
   h->opt.block = o.block;
   h->opt.depth = o.depth;
@@ -1300,13 +1297,12 @@ int rg_autotune(rg_handle* h, const double* x0, double v0, const double* r_seq, 
   int rc = ensure_workspace(h);
   if (rc) return rc;
   const rg_options own = h->opt;
-  const bool own_auto = h->auto_depth;
   const uint32_t t0 = h->t;
   const bool f32_robust = h->opt.precision == RG_PREC_F32_RECHECK && h->opt.chance_q == 0;
   const bool quad_ok = h->pr.p.kind == RG_PLANT_LQ4 && f32_robust;
   const bool group_ok =
       h->pr.p.kind == RG_PLANT_FC9 && f32_robust && h->opt.search != RG_SEARCH_NEWTON_TAN;
-  std::vector<rg_options> cands;
+  std::vector<rg_options> cands{own};  // the schedule in force first
   for (int lanes : {4, 16, 1}) {
     if (lanes == 4 && !quad_ok) continue;
     if (lanes == 16 && !group_ok) continue;
@@ -1335,7 +1331,7 @@ int rg_autotune(rg_handle* h, const double* x0, double v0, const double* r_seq, 
   double best_ms = INFINITY;
   rg_options best = own;
   for (const rg_options& o : cands) {
-    if ((rc = apply_schedule(h, o, false))) break;
+    if ((rc = apply_schedule(h, o))) break;
     // the first run captures the graphs; the faster of the next two counts
     double ms = INFINITY;
     for (int rep = 0; rep < 3 && rc == RG_OK; ++rep) {
@@ -1362,8 +1358,7 @@ int rg_autotune(rg_handle* h, const double* x0, double v0, const double* r_seq, 
   }
   h->t = t0;
   h->gen_t = -1;  // the streamed draws no longer match the step counter
-  const bool keep = rc == RG_OK && apply;
-  const int rc2 = apply_schedule(h, keep ? best : own, !keep && own_auto);
+  const int rc2 = apply_schedule(h, (rc == RG_OK && apply) ? best : own);
   if (rc) return rc;
   if (rc2) return rc2;
   if (best_out) *best_out = best;
@@ -1807,10 +1802,9 @@ int rg_batch_create(const rg_instance_desc* descs, int32_t count, const rg_optio
       delete bt;
       return bfail(nullptr, rc, m);
     }
-    if (o.depth == 0 && lanes <= kBatchPathTo) {
-      h->batch_path = std::min(goal, kBatchPath);
-      plan(h);
-    }
+    h->member = true;
+    h->batch_path = lanes <= kBatchPathTo ? std::min(goal, kBatchPath) : 0;
+    plan(h);
     bt->inst.push_back(h);
     bt->noff.push_back(noff);
     noff += h->pr.p.n;
