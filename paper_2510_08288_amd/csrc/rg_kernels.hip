@@ -1526,6 +1526,8 @@ __global__ void __launch_bounds__(128) k_setup_list(const CtlArgs<KIND> a, int M
     S->done = 0;
     S->n_cand = M;
     S->round = 0;
+    S->spec_n = 0;  // a closed loop may have ended on steps decided ahead
+    S->spec_used = 0;
   }
   __syncthreads();
   prepare_candidates<KIND>(a.pc, a.st, S);
