@@ -236,7 +236,8 @@ typedef struct rg_batch rg_batch;
 /* One independent governor of a batch. */
 typedef struct rg_instance_desc {
     rg_plant plant;
-    rg_scenarios scen;     /* rng_mode is ignored: batches draw inline */
+    rg_scenarios scen;     /* rng_mode RG_RNG_INLINE: draws regenerated in the kernels, no
+                              memory for them (else: see rg_batch_create) */
     rg_constraints cons;
     int32_t H;
     double dt;
@@ -433,12 +434,12 @@ int rg_equilibrium(rg_handle* h, double v, double* x_out);
 /* A batch of `count` independent governors (own plant, scenarios, constraints,
  * H and dt each; the paper notes one small governor gains little from a GPU,
  * Sec. IV-B).  Each instance keeps its own search record and FP64 recheck list
- * in one device allocation; the draws of all instances (4 B x N x H x n_w
- * each) are generated once per step into a second one where they fit in 16 GiB
- * and a quarter of the free memory, and regenerated inside the kernels otherwise
- * (the scenarios' rng_mode is ignored; results are the same).  One search round
- * of the instances with the same plant kind, injection and rollout layout is one
- * flat rollout launch (all their scenario tiles in one grid, FP32, one lane per
+ * in one device allocation; the draws of the instances with streamed draws (4 B
+ * x N x H x n_w each) are generated once per step into a second one where they
+ * all fit in 16 GiB and a quarter of the free memory, kept as long as the batch,
+ * and regenerated inside the kernels otherwise and for the other instances
+ * (results are the same).  One search round of the instances with the same plant
+ * kind, injection, draws and rollout layout is one flat rollout launch (all their scenario tiles in one grid, FP32, one lane per
  * scenario, or for the longest horizons of the 9-state plant a group of lanes),
  * then their FP64 rechecks and decisions.  All instances
  * use one search depth (opt.depth = 0: from the sum of N over the batch) and, up

@@ -1453,11 +1453,11 @@ int rg_trajectory(rg_handle* h, const double* x, double v, const int32_t* k_list
 // ---------------------------------------------------------------------------
 // Many independent governors stepped together.  Each instance keeps its own
 // search record, result record and recheck list, carved from one device
-// allocation.  Its draws are generated once per step into a second allocation
-// where all of them fit in kBatchDrawBytes, else regenerated inside the kernels
-// (a batch of a thousand instances could not hold draw buffers).  One search
-// round of a group of instances (same plant kind, disturbance injection and
-// rollout layout) is one flat rollout launch (every instance's scenario tiles
+// allocation.  The draws of the instances that ask for streamed ones are generated
+// once per step into a second allocation where all of them fit in kBatchDrawBytes,
+// else regenerated inside the kernels (a batch of a thousand instances could not
+// hold draw buffers).  One search round of a group of instances (same plant kind,
+// disturbance injection, draws and rollout layout) is one flat rollout launch (every instance's scenario tiles
 // side by side in one grid, each workgroup reading its instance's argument block
 // from device memory), then one flat launch for the FP64 recheck and the round's
 // decision.  A group's step starts with its instances' round-0 setup and ends
@@ -1467,7 +1467,7 @@ int rg_trajectory(rg_handle* h, const double* x, double v, const int32_t* k_list
 constexpr double kBatchDrawBytes = 16.0 * (1 << 30);
 constexpr int kBatchSide = 3;  // streams beside the batch's own
 struct BatchGroup {
-  int kind = 0, inject = 0, lanes = 1, tiles = 0, cmax = 0, rounds = 0;
+  int kind = 0, inject = 0, lanes = 1, streams = 0, tiles = 0, cmax = 0, rounds = 0;
   std::vector<int> members;     // batch indices of the group's instances
   void* args = nullptr;         // device: the members' FP32 rollout argument blocks
   void* args64 = nullptr;       // device: their FP64 recheck argument blocks
@@ -1483,6 +1483,7 @@ struct rg_batch {
   std::vector<rg_handle*> inst;  // per instance: problem, plan and carved buffers
   std::vector<int> noff;         // offset of each instance's state in the packed x array
   std::vector<uint32_t> t;       // per-instance RG step counters
+  std::vector<char> streams;     // instances that ask for streamed draws
   std::vector<BatchGroup> groups;
   int tile = 256;                // scenarios per rollout workgroup
   hipStream_t stream = nullptr;  // the caller's stream (NULL: own_stream)
@@ -1574,6 +1575,7 @@ int batch_ensure_memory(rg_batch* bt) {
   std::vector<size_t> o_w(count), o_th(count);
   size_t doff = 0;
   for (int i = 0; i < count; ++i) {
+    if (!bt->streams[i]) continue;
     const Problem& pr = bt->inst[i]->pr;
     o_w[i] = doff;
     doff = align256(doff + sizeof(float) * (size_t)pr.H * pr.p.nw * pr.s.N);
@@ -1581,7 +1583,7 @@ int batch_ensure_memory(rg_batch* bt) {
     doff = align256(doff + sizeof(float) * (size_t)pr.p.nth * pr.s.N);
   }
   size_t mfree = 0, mtotal = 0;
-  if ((double)doff <= kBatchDrawBytes && hipMemGetInfo(&mfree, &mtotal) == hipSuccess &&
+  if (doff > 0 && (double)doff <= kBatchDrawBytes && hipMemGetInfo(&mfree, &mtotal) == hipSuccess &&
       doff <= mfree / 4 && hipMalloc(&bt->draws, doff) != hipSuccess) {
     bt->draws = nullptr;
     (void)hipGetLastError();
@@ -1598,7 +1600,7 @@ int batch_ensure_memory(rg_batch* bt) {
     b.srch = srch + i;
     b.res = bt->res + i;
     b.rlist = (int2*)(base + o_rl[i]);
-    if (bt->draws) {
+    if (bt->draws && bt->streams[i]) {
       b.wbuf = (float*)((char*)bt->draws + o_w[i]);
       b.thbuf = (float*)((char*)bt->draws + o_th[i]);
     }
@@ -1658,7 +1660,7 @@ int batch_ensure_memory(rg_batch* bt) {
 
 // One group's whole step on stream gs.
 hipError_t batch_enqueue_group(const rg_batch* bt, const BatchGroup& G, hipStream_t gs) {
-  const int nm = (int)G.members.size(), rng = bt->draws ? 0 : 1;
+  const int nm = (int)G.members.size(), rng = bt->draws && G.streams ? 0 : 1;
   hipError_t e = rng ? hipSuccess : launch_flat_gen(G.kind, G.args, nm, gs);
   if (e == hipSuccess) e = launch_flat_setup(G.kind, G.ctl, nm, gs);
   for (int r = 0; r < G.rounds && e == hipSuccess; ++r) {
@@ -1806,25 +1808,32 @@ int rg_batch_create(const rg_instance_desc* descs, int32_t count, const rg_optio
     h->batch_path = lanes <= kBatchPathTo ? std::min(goal, kBatchPath) : 0;
     plan(h);
     bt->inst.push_back(h);
+    bt->streams.push_back(descs[i].scen.rng_mode == RG_RNG_INLINE ? 0 : 1);
     bt->noff.push_back(noff);
     noff += h->pr.p.n;
   }
   double draw_bytes = 0.0;
-  for (const rg_handle* h : bt->inst)
-    draw_bytes += 4.0 * h->pr.s.N * ((double)h->pr.H * h->pr.p.nw + h->pr.p.nth);
-  const int theta = batch_group_horizon(bt->inst, draw_bytes <= kBatchDrawBytes);
-  for (int i = 0; i < count; ++i) {  // groups: plant kind, injection, layout
+  for (int i = 0; i < count; ++i) {
+    const rg_handle* h = bt->inst[i];
+    if (bt->streams[i]) draw_bytes += 4.0 * h->pr.s.N * ((double)h->pr.H * h->pr.p.nw + h->pr.p.nth);
+  }
+  const int theta =
+      batch_group_horizon(bt->inst, draw_bytes > 0.0 && draw_bytes <= kBatchDrawBytes);
+  for (int i = 0; i < count; ++i) {  // groups: plant kind, injection, draws, layout
     const rg_handle* h = bt->inst[i];
     const int lanes = h->pr.p.kind == RG_PLANT_FC9 && h->pr.H > theta ? 16 : 1;
     BatchGroup* G = nullptr;
     for (BatchGroup& g : bt->groups)
-      if (g.kind == h->pr.p.kind && g.inject == h->pr.s.inject && g.lanes == lanes) G = &g;
+      if (g.kind == h->pr.p.kind && g.inject == h->pr.s.inject && g.lanes == lanes &&
+          g.streams == bt->streams[i])
+        G = &g;
     if (!G) {
       bt->groups.emplace_back();
       G = &bt->groups.back();
       G->kind = h->pr.p.kind;
       G->inject = h->pr.s.inject;
       G->lanes = lanes;
+      G->streams = bt->streams[i];
     }
     G->members.push_back(i);
     const int tile = flat_tile(lanes, bt->tile);

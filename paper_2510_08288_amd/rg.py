@@ -433,9 +433,10 @@ class Governor:
         return out
 
 
-def _batch_descs(problems):
+def _batch_descs(problems, rng_mode=RNG_STREAM):
     """Instance descriptors of a batch, and the arrays they point into (keep them alive)."""
     keep = []
+    rng_mode = np.broadcast_to(rng_mode, len(problems))
     descs = (rg_instance_desc * len(problems))()
     for i, p in enumerate(problems):
         co, wlo, whi = _f64(p.coeffs), _f64(p.w_lo), _f64(p.w_hi)
@@ -444,7 +445,7 @@ def _batch_descs(problems):
         descs[i].plant = rg_plant(p.kind, p.n, p.n_w, p.n_y, p.n_theta, _ptr(co), co.size)
         descs[i].scen = rg_scenarios(int(p.N), int(p.seed) & 0xFFFFFFFF,
                                      int(p.instance) & 0xFFFFFFFF, _ptr(wlo), _ptr(whi),
-                                     float(p.theta_rel), int(p.inject), RNG_INLINE)
+                                     float(p.theta_rel), int(p.inject), int(rng_mode[i]))
         descs[i].cons = rg_constraints(int(np.asarray(p.F).shape[0]), _ptr(F), _ptr(g),
                                        float(p.eps), int(p.ss_check))
         descs[i].H = int(p.H)
@@ -462,12 +463,12 @@ def _batch_options(K, band, depth, block, persistent_wgs, early_exit, predict, s
 
 def batch_autotune(problems, xs, r, v_prev, K: int = 12, band: float = 1e-4,
                    early_exit: bool = True, search: int = SEARCH_BISECT, M: int = 64,
-                   refine: int = 6) -> dict:
+                   refine: int = 6, rng_mode=RNG_STREAM) -> dict:
     """rg_batch_autotune: time steps 0..2 of the batch under every schedule
     (scenario tile, depth, first-round prediction) and return the fastest one
     (keyword arguments of Batch) with its time per batched step."""
     L = load_library()
-    descs, keep = _batch_descs(problems)
+    descs, keep = _batch_descs(problems, rng_mode)
     opt = _batch_options(K, band, 0, 64, 0, early_exit, False, search, M, refine)
     x = _f64(np.concatenate([np.asarray(v, dtype=np.float64) for v in xs]))
     r = _f64(r)
@@ -483,15 +484,17 @@ def batch_autotune(problems, xs, r, v_prev, K: int = 12, band: float = 1e-4,
 
 
 class Batch:
-    """Many independent governors stepped together (``rg_batch_*``)."""
+    """Many independent governors stepped together (``rg_batch_*``).  rng_mode: one mode, or one
+    per problem; RNG_INLINE instances regenerate their draws and take no memory for them."""
 
     def __init__(self, problems, K: int = 12, band: float = 1e-4, depth: int = 0, block: int = 0,
                  persistent_wgs: int = 0, early_exit: bool = True, predict: bool = False,
-                 search: int = SEARCH_BISECT, M: int = 64, refine: int = 6):
+                 search: int = SEARCH_BISECT, M: int = 64, refine: int = 6,
+                 rng_mode=RNG_STREAM):
         import torch
         self.L = load_library()
         self.problems = list(problems)
-        descs, self._keep = _batch_descs(self.problems)
+        descs, self._keep = _batch_descs(self.problems, rng_mode)
         opt = _batch_options(K, band, depth, block, persistent_wgs, early_exit, predict, search,
                              M, refine)
         h = _vp()
