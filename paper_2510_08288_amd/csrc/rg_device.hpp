@@ -762,17 +762,16 @@ __device__ __forceinline__ T margin_row(const T* F, const T* g, const T* y, int 
   return m;
 }
 
-// Margin and its minimising row (the derivative kernels).
+// Margin and its minimising row, each row as margin_rows takes it (a NaN row
+// stays).
 template <int NY, class T>
 __device__ __forceinline__ T margin_rows_arg(const T* F, const T* g, const T* y, int& rarg) {
   T best = t_inf<T>();
   rarg = 0;
 #pragma unroll
   for (int r = 0; r < kNC; ++r) {
-    T fy = F[r * NY] * y[0];
-#pragma unroll
-    for (int i = 1; i < NY; ++i) fy = t_fma(F[r * NY + i], y[i], fy);
-    const T m = g[r] - fy;
+    const T m = NY == 2 ? g[r] - t_fma(F[r * NY + 1], y[1], F[r * NY] * y[0])
+                        : margin_row<NY>(F, g, y, r);
     if (m < best || m != m) {
       best = m;
       rarg = r;

@@ -154,7 +154,18 @@ struct AdjLanes {
     y[0] = a.pc.c_q0 * X6 / t_fma(a.pc.d1, slot[11], a.pc.d0);
     y[1] = X0;
     y[2] = X6;
-    return margin_rows_arg<P::ny>(a.F, a.g, y, r);
+    float best = INFINITY;
+    r = 0;
+#pragma unroll
+    for (int q = 0; q < kNC; ++q) {
+      const float* F = a.F + q * P::ny;
+      const float m = a.g[q] - t_fma(F[2], y[2], t_fma(F[1], y[1], F[0] * y[0]));
+      if (m < best || m != m) {
+        best = m;
+        r = q;
+      }
+    }
+    return best;
   }
   // What the reverse sweep keeps of one stage's point.
   struct Point {
