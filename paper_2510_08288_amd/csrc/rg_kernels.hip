@@ -2210,11 +2210,12 @@ __global__ void k_traj(const RollArgs<KIND, T> a, T v, const int32_t* k_list, in
 // every Kc steps (tracking the minimiser j*, r*), then segment by segment from
 // j* back to 0: recompute the segment's states from its checkpoint, sweep them
 // in reverse with rk4_vjp.  States and adjoints in FP32, parameter sums in
-// FP64.  One lane per (scenario, upstream weight) entry.
+// FP64.  One lane per (scenario, upstream weight) entry; the 9-state plant's form
+// is in rg_fc9_adj.hip.
 // ---------------------------------------------------------------------------
-template <int KIND, int RNG, int INJ>
-__global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, const AdjArgs g) {
-  using P = Plant<KIND, float>;
+template <int RNG, int INJ>
+__global__ void __launch_bounds__(64) k_adjoint_lq4(const RollArgs<1, float> a, const AdjArgs g) {
+  using P = Plant<1, float>;
   constexpr int n = P::n;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= g.grad->n_entries) return;
@@ -2225,20 +2226,8 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
   if ((a.srch->done || cand < 0) && g.cand < 0) return;
   const float v = (float)a.srch->v[cand];
   const size_t L = (size_t)g.lmax;
-  float th[P::nth > 0 ? P::nth : 1], fac[P::nth > 0 ? P::nth : 1];
-  if constexpr (P::nth > 0) {
-    if (RNG == 0) {
-      const float* tb = step_th(a, t);
-      for (int c = 0; c < P::nth; ++c) fac[c] = tb[(size_t)c * a.N + k];
-    } else {
-      draw_theta_factor<P::nth>(a.seed, a.inst, t, (uint32_t)k, a.thlo, a.thspan, fac);
-    }
-    for (int c = 0; c < P::nth; ++c) th[c] = a.pc.thnom[c] * fac[c];
-  }
-  typename P::Lane Ln;
-  P::lane_init(a.pc, th, v, Ln);
-  float wv[KIND == 2 ? 81 : 1];
-  w_in_vgprs<KIND, 81>(a.pc, wv, Ln);
+  P::Lane Ln;
+  P::lane_init(a.pc, nullptr, v, Ln);
   const float* wb = RNG == 0 ? step_w(a, t) : nullptr;
   auto load_w = [&](int j, float* w) {
     if (RNG == 0) {
@@ -2254,7 +2243,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
   auto step = [&](float* x, const float* w) {
     float s[n];
     forcing(w, s);
-    rk4_step<KIND, float>(a.pc, Ln, s, a.h, a.hh, a.h6, x);
+    rk4_step<1, float>(a.pc, Ln, s, a.h, a.hh, a.h6, x);
     if (INJ == 1) P::post(a.pc, w, x);
   };
   // forward: minimiser and checkpoints
@@ -2285,8 +2274,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
   bool finite = best == best;
   for (int i = 0; i < n; ++i) finite = finite && (x[i] - x[i] == 0.f);
   double vb = 0.0;
-  double tb[P::nth > 0 ? P::nth : 1];
-  for (int c = 0; c < (P::nth > 0 ? P::nth : 1); ++c) tb[c] = 0.0;
+  double tb[1] = {0.0};  // no uncertain coefficients
   if (finite) {
     float lam[n];
     P::out_grad(a.pc, a.F + rb * P::ny, xbest, lam);
@@ -2305,7 +2293,7 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
         load_w(j, w);
         float s[n];
         forcing(w, s);
-        rk4_vjp<KIND, float>(a.pc, Ln, s, a.h, a.hh, a.h6, xs, lam, vb, tb);
+        rk4_vjp<1, float>(a.pc, Ln, s, a.h, a.hh, a.h6, xs, lam, vb, tb);
       }
     }
   } else {
@@ -2313,7 +2301,6 @@ __global__ void __launch_bounds__(64) k_adjoint(const RollArgs<KIND, float> a, c
   }
   g.out_m[e] = best;
   g.out_dv[e] = (double)wgt * vb;
-  for (int c = 0; c < P::nth; ++c) g.out_dth[(size_t)e * kMaxTh + c] = (double)wgt * tb[c] * (double)fac[c];
   if (e == 0) {
     g.grad->j_star = jb;
     g.grad->r_star = rb;
@@ -3062,7 +3049,7 @@ hipError_t launch_adjoint(const Problem& pr, int Kc, int max_entries, const DevB
     return by_bit(pr.s.inject, [&](auto ic) {
       constexpr int I = decltype(ic)::value;
       auto a = make_args<1, float>(pr, 0.0, 0, 0, b);
-      hipLaunchKernelGGL((k_adjoint<1, R, I>), dim3(div_up(max_entries, 64)), dim3(64), 0, st, a, g);
+      hipLaunchKernelGGL((k_adjoint_lq4<R, I>), dim3(div_up(max_entries, 64)), dim3(64), 0, st, a, g);
       return hipGetLastError();
     });
   });
