@@ -427,17 +427,21 @@ struct Plant<2, T> {
     else return t_tanh<IEEE>(x - xbar);
   }
   // Row i of the derivative: s_i - K R - A x_i + W_i . act + P Q, one fma per
-  // term in this order, nothing contracted, so that the one-lane derivative and
-  // the lane groups (one lane per row) round alike.  The terms per row:
+  // term in this order, nothing contracted, for the one-lane derivative and the
+  // lane groups (one lane per row) alike.  The terms per row:
   //   i < 6:  K R = k_i r_i (the flow out), P Q = c_q0 x_7 (i = 0) or the flow in
   //   i = 6:  P Q = -(mu_1 x_7) (x_1 - p1ref);  i = 7: b_2 v x_7;  i = 8: none
-  __device__ static T row(T s, T K, T R, T A, T xi, const T* wrow, const T* act, T Pq, T Q) {
+  // KR, PQ: the row has the term (the one-lane derivative leaves out what is zero;
+  // a group's lanes differ by data only).
+  template <bool KR = true, bool PQ = true>
+  __device__ __forceinline__ static T row(T s, T K, T R, T A, T xi, const T* wrow, const T* act,
+                                          T Pq, T Q) {
 #pragma clang fp contract(off)
-    T a = t_fma(-K, R, s);
+    T a = KR ? t_fma(-K, R, s) : s;
     a = t_fma(-A, xi, a);
 #pragma unroll
     for (int j = 0; j < 9; ++j) a = t_fma(wrow[j], act[j], a);
-    return t_fma(Pq, Q, a);
+    return PQ ? t_fma(Pq, Q, a) : a;
   }
   // Square-root factor of the orifice flow q_{l+1}: sqrt(max(p_l - p_{l+1}, 0))
   // with p_7 = p_amb.
@@ -457,15 +461,16 @@ struct Plant<2, T> {
     for (int l = 0; l < 6; ++l) r[l] = orifice<IEEE>(x[l], (l < 5) ? x[l + 1] : c.p_amb);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-      T a = s[i];
-      if (i < 6) a = t_fma(-L.kq[i < 6 ? i : 0], r[i < 6 ? i : 0], a);
-      a = t_fma(-(i < 8 ? L.a[i] : L.a9), x[i], a);
-#pragma unroll
-      for (int j = 0; j < 9; ++j) a = t_fma(L.W[9 * i + j], tz[j], a);
-      if (i == 0) a = t_fma(c.c_q0, x[6], a);
-      else if (i < 6) a = t_fma(L.kq[i - 1], r[i - 1], a);
-      else if (i == 6) a = t_fma(-(L.mu[0] * x[6]), x[0] - c.p1ref, a);
-      else if (i == 7) a = t_fma(L.b2v, x[6], a);
+      const T* w = &L.W[9 * i];
+      T a;
+      if (i == 0) a = row(s[0], L.kq[0], r[0], L.a[0], x[0], w, tz, c.c_q0, x[6]);
+      else if (i < 6)
+        a = row(s[i], L.kq[i < 6 ? i : 0], r[i < 6 ? i : 0], L.a[i], x[i], w, tz,
+                L.kq[i > 0 && i < 7 ? i - 1 : 0], r[i > 0 && i < 7 ? i - 1 : 0]);
+      else if (i == 6)
+        a = row<false>(s[6], 0, 0, L.a[6], x[6], w, tz, -(L.mu[0] * x[6]), x[0] - c.p1ref);
+      else if (i == 7) a = row<false>(s[7], 0, 0, L.a[7], x[7], w, tz, L.b2v, x[6]);
+      else a = row<false, false>(s[8], 0, 0, L.a9, x[8], w, tz, 0, 0);
       xd[i] = a;
     }
   }
