@@ -164,9 +164,10 @@ typedef struct rg_options {
                               of lanes, one lane per state component; robust verdict, not
                               with the tangent-driven Newton search); 0 = auto (LQ4: 4; FC9:
                               16 while a round holds few scenario-candidate pairs (grid: at
-                              most 98304, else 32768), else 1).  FP64 rollouts have one
-                              layout each (LQ4: 4 lanes, FC9: groups), whatever this says.  kappa is the same in every layout; the 9-state
-                              groups' margins are bit-identical to one lane's */
+                              most 98304, Newton 49152, else 32768), else 1).  FP64
+                              rollouts have one layout each (LQ4: 4 lanes, FC9: groups),
+                              whatever this says.  kappa is the same in every layout; the
+                              9-state groups' margins are bit-identical to one lane's */
     int32_t Kc;            /* adjoint checkpoint interval in RK4 steps (default 50) */
     int32_t persistent_wgs;/* batches: workgroups of the persistent rollout kernel (0 = auto) */
     int32_t predict;       /* bisection: 1 (default) makes the first device round of a step

@@ -180,16 +180,18 @@ Layout layout_of(const rg_handle* h) {
 // round they run one scenario per group of lanes: one lane per scenario leaves
 // the chip mostly idle there, and each round is bound by the latency of a whole
 // RK4 step on one lane; with more pairs the groups' exchanges cost more than
-// the latency they save.  Grid (rows die early): the 32-point grid at N = 2048
-// H = 700 takes 1.11 ms with groups and 1.63 with one lane, 1.46 and 1.53 at
-// N = 4096.  Bisection, in rounds of depth 2: N = 4096 H = 700 4.4 and 5.4 ms
-// per update, N = 8192 5.3 and 6.4, N = 16384 8.1 and 7.9.  Newton: rounds of
-// four candidates, one of them over the full horizon.
-constexpr double kGroupPairsGrid = 98304, kGroupPairs = 32768;
+// the latency they save.  One update at H = 700, groups and one lane: grid (rows
+// die early; the line lies well inside the groups' range, which ends at about
+// 180000 pairs) 32 points N = 2048 0.75 and 1.57 ms, N = 3072 1.03 and 1.57, N = 5120
+// 1.36 and 1.58, N = 6144 1.55 and 1.61.  Bisection, in rounds of depth 2: N = 4096
+// 3.2 and 4.9, N = 8192 4.3 and 5.4, N = 10922 5.6 and 5.2 (first updates 5.0 and 5.9),
+// N = 14000 6.5 and 6.4.  Newton, rounds of four candidates, one of them over the full
+// horizon: N = 8192 7.1 and 9.9, N = 12288 9.1 and 10.7, N = 16384 10.9 and 10.5.
+constexpr double kGroupPairsGrid = 98304, kGroupPairs = 32768, kGroupPairsNewton = 49152;
 bool groups_pay(const rg_handle* h) {
   const double N = h->pr.s.N;
   if (h->opt.search == RG_SEARCH_GRID) return h->opt.M * N <= kGroupPairsGrid;
-  return (is_newton(h->opt.search) ? 4 : 3) * N <= kGroupPairs;
+  return is_newton(h->opt.search) ? 4 * N <= kGroupPairsNewton : 3 * N <= kGroupPairs;
 }
 
 int lanes_for(const rg_handle* h) {
@@ -208,13 +210,17 @@ int lanes_for(const rg_handle* h) {
 // Waves one candidate of a round occupies, and the waves per round up to which
 // more candidates cost little: a round is then bound by one wave's chain of
 // steps, and beyond it they cost their full time.  Two per SIMD for the 4-state
-// plant (quads and matrix layout alike) and the 9-state FP64 groups, 4.5 for the
-// 9-state FP32 groups, one for the 9-state one-lane rollouts (which keep the
-// vector ALU busy at one).  Per update, FP64 4-state: N = 1024 H = 1000 depth
-// 3 / 4 / 5: 0.61 / 0.52 / 0.58 ms, N = 4096 H = 2000 depth 2 / 3 / 4: 1.57 /
-// 1.48 / 1.65; 9-state H = 700, groups: N = 2048 depth 3 / 4 3.7 / 3.4 ms, N =
-// 8192 depth 2 / 3 5.3 / 5.6; FP64: N = 512 depth 3 / 4 / 5 3.8 / 3.3 / 3.4 ms;
-// one lane: N = 16384 depth 2 / 3 / 4 7.9 / 8.2 / 8.6.
+// plant (quads and matrix layout alike), 1.9 for the 9-state FP64 groups and 4.2 for
+// the FP32 ones, one for the 9-state one-lane rollouts (which keep the vector ALU
+// busy at one).  Per update, FP64 4-state: N = 1024 H = 1000 depth 3 / 4 / 5: 0.61 /
+// 0.52 / 0.58 ms, N = 4096 H = 2000 depth 2 / 3 / 4: 1.57 / 1.48 / 1.65; 9-state H =
+// 700 (with the path to the predicted root, which leaves less to the depth), repeated
+// and first updates: groups N = 2048 depth 3 / 4 2.46 and 2.73 / 2.97 and 2.92 ms, N =
+// 4096 depth 2 / 3 / 4 3.2 and 3.5 / 3.2 and 3.3 / 4.4, N = 8192 depth 2 / 3 4.4 and
+// 4.0 / 4.9 and 4.0; FP64 N = 1000 depth 2 / 3 / 4 2.4 and 3.2 / 2.2 and 2.6 / 3.1 and
+// 2.5, N = 2048 depth 2 / 3 2.9 and 3.4 / 3.4 and 3.4; one lane N = 16384 depth 1 / 2 /
+// 3 / 4 6.6 and 7.9 / 6.5 and 6.5 / 7.0 and 7.5 / 7.4 and 7.1, N = 49152 depth 1 / 2 / 3
+// 10.6 and 9.7 / 10.8 and 10.1 / 10.9 and 10.6.
 double waves_per_candidate(const rg_handle* h, int lanes) {
   const double N = h->pr.s.N;
   if (h->pr.p.kind == RG_PLANT_FC9)  // groups: seven scenarios per wave
@@ -223,8 +229,8 @@ double waves_per_candidate(const rg_handle* h, int lanes) {
 }
 double wave_budget(const rg_handle* h, int lanes) {
   double per_simd = 2.0;
-  if (h->pr.p.kind == RG_PLANT_FC9 && h->opt.precision != RG_PREC_F64)
-    per_simd = lanes == 16 ? 4.5 : 1.0;
+  if (h->pr.p.kind == RG_PLANT_FC9)
+    per_simd = h->opt.precision == RG_PREC_F64 ? 1.9 : (lanes == 16 ? 4.2 : 1.0);
   return per_simd * 256 * 4;
 }
 
