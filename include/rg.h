@@ -440,13 +440,14 @@ int rg_equilibrium(rg_handle* h, double v, double* x_out);
  * all fit in 16 GiB and a quarter of the free memory, kept as long as the batch,
  * and regenerated inside the kernels otherwise and for the other instances
  * (results are the same).  One search round of the instances with the same plant
- * kind, injection, draws and rollout layout is one flat rollout launch (all their scenario tiles in one grid, FP32, one lane per
- * scenario, or for the longest horizons of the 9-state plant a group of lanes),
- * then their FP64 rechecks and decisions.  All instances
- * use one search depth (opt.depth = 0: from the sum of N over the batch) and, up
- * to 2^20 scenarios in all, rounds along the predicted bisection path; large
- * batches evaluate one candidate per round.  opt: precision F32_RECHECK,
- * search BISECT or GRID, chance_q 0 (else RG_E_NOTSUP); block is the scenario
+ * kind, injection, draws and rollout layout is one flat rollout launch (all
+ * their scenario tiles in one grid, FP32, one lane per scenario, or for the
+ * longest horizons of the 9-state plant a group of lanes), then their FP64
+ * rechecks and decisions.  All instances use one search depth (opt.depth = 0:
+ * from the sum of N over the batch) and, up to 2^20 scenarios in all, rounds
+ * along the predicted bisection path; large batches evaluate one candidate per
+ * round.  opt: precision F32_RECHECK, search BISECT or GRID, chance_q 0 (else
+ * RG_E_NOTSUP); block is the scenario
  * tile (64, 128, 256); predict as for rg_create; persistent_wgs is accepted
  * and unused.  opt = NULL: the defaults of rg_default_options except block =
  * 64 and predict = 0 (a batch's rounds are throughput-bound, so the least
@@ -505,7 +506,8 @@ int rg_trajectory(rg_handle* h, const double* x, double v, const int32_t* k_list
                   int32_t precision, double* traj);
 
 /* The FP64 tanh the FP64 rollouts, rechecks and steady-state solves of the
- * 9-state plant use, evaluated on the current device for x[0..n) into y
+ * 9-state plant use (Alg. 2's table of them: the same with an IEEE quotient),
+ * evaluated on the current device for x[0..n) into y
  * (host arrays; for tests of its accuracy).  Blocking; allocates and frees
  * device memory. */
 int rg_fp64_tanh(const double* x, double* y, int32_t n);
